@@ -92,3 +92,29 @@ def test_device_lookahead_rejects_a_short_workspace(stream_case):
         om.ordermoe_build_lookahead_device(1, None, x, None, None, None, None, None, None, None, None, None,
                                            0.5, 0.5, 1.0, ws=ws)
     assert ei.value.code == om.EWORKSPACE
+
+
+@pytest.mark.parametrize("N,E,M,T,H,pin,allow_sub", [
+    (2, 1, 1, 3, 2, 1, 1),            # one expert, one server
+    (3, 65, 3, 32768, 3, 0, 1),       # one expert past a wave; the longest calibration counted in LDS
+    (2, 64, 5, 32769, 4, 1, 2),       # the first one counted in device memory
+    (4, 256, 32, 700, 3, 0, 1),       # the maximum sizes
+])
+def test_device_tables_equal_the_host_at_the_edges(N, E, M, T, H, pin, allow_sub):
+    """P and Phi on the device equal the host library's bit for bit at the
+    bounds of the row, mask and tile splits."""
+    rng = np.random.default_rng(E * 100 + M)
+    top1 = rng.integers(0, E, size=(N, T)).astype(np.int32)
+    P = om.ordermoe_estimate_transitions(top1, E)
+    np.testing.assert_array_equal(om.ordermoe_estimate_transitions_device(_dev(top1), E).cpu().numpy(), P)
+    x = (rng.random((N, M, E)) < 0.3).astype(np.uint8)
+    x[:, rng.integers(0, M, E), np.arange(E)] = 1
+    sim = rng.uniform(0.3, 1.0, (N, E, E)).astype(np.float32)
+    group = rng.integers(0, max(E // 7, 1), size=(N, E)).astype(np.int32)
+    theta = rng.uniform(0.4, 0.8, N).astype(np.float32)
+    z, c, d_ref = rng.uniform(1e5, 1e6, N), rng.uniform(1e9, 1e10, (N, E)), rng.uniform(1e-5, 1e-4, N)
+    B, tau, F = rng.uniform(1e9, 1e10, (M, M)), rng.uniform(1e-4, 1e-2, (M, M)), rng.uniform(2e13, 1e14, M)
+    args = (P, x, sim, group, theta, z, c, d_ref, B, tau, F)
+    want = om.ordermoe_build_lookahead(H, *args, 0.5, 0.5, 0.25, pin, allow_sub)
+    got = om.ordermoe_build_lookahead_device(H, *(_dev(a) for a in args), 0.5, 0.5, 0.25, pin, allow_sub)
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
