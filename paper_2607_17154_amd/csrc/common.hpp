@@ -69,7 +69,7 @@ struct RouteArgs {
     int nblk;
     int S_in_lds;          // set by the launcher: stage the cost table in LDS
     int ksplit;            // set by the launcher: K slices of the split router (0: fused)
-    int x_lds;             // set by the launcher: bytes of the LDS-staged token rows (0: none)
+    int x_lds;             // set by the launcher: bytes of the LDS-staged token rows (0: none); fp32: the router's LDS
 };
 int launch_route_select(const RouteArgs& a, void* stream);
 int route_tokens_per_block();
