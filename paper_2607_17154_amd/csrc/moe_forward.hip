@@ -1121,84 +1121,167 @@ ggemm_thin(const GemmArgs p) {
     }
 }
 
-// fp32 storage: plain LDS-tiled FMA GEMM, 64 x 64 tiles, 4 x 4 outputs per thread
-template <int MODE>
-__global__ void __launch_bounds__(256) ggemm_f32(const GemmArgs p) {
-    constexpr int BM = 64, BN = 64, BK = 16;
-    __shared__ float sA[BK][BM + 4];
-    __shared__ float sB[BK][BN + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int total = *p.ntiles;
-    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+// fp32 storage: C = A B^T per tile of BM x 64 by v_mfma_f32_32x32x2_f32, whose
+// products and sums are the fp32 FMA's.  4 waves: BM / 32 row blocks x 2 column
+// blocks of 32 x KW slices of K, so a tile occupies all four matrix units of a
+// CU whatever its height; the slices' sums meet in LDS and are added in slice
+// order.  A K step is KW slices of 32 floats; the rows of a slice (128 bytes)
+// go from memory straight into LDS with the 16-byte chunks permuted as in
+// ggemm_bf16, three buffers, the loads of a step issued two steps ahead.  A
+// fragment read is 16 bytes: chunk 2 q + lane / 32 holds the K values 8 q + 4
+// (lane / 32) .. +3 of its row, which feed four MFMAs.  Two workgroups share a
+// CU, so that one's fragment reads and epilogue run beside the other's MFMAs.
+// Two shapes: 64-row tiles, and 32-row tiles with two K slices when the 64-row
+// tiles would leave CUs without work (fewer than F32_TALL_TILES in all); the
+// choice is made here, from the row counts on the device.  What bounds it is
+// the fp32 matrix rate (157 TFLOP/s) at many rows, and at a few hundred rows
+// the length of one tile's K loop.  Measured against 64 x 64 tiles of scalar
+// loads and vector FMAs: 290 rows, d = 512, f = 1024: gate/up 59 -> 15 us, down
+// 145 -> 14 us; 641 rows, d = 1024, f = 640: 131 -> 26 and 98 -> 19 us.
+constexpr int F32_BM = 64, F32_BN = 64, F32_THREADS = 256, F32_PER_CU = 2;
+constexpr int F32_TALL_TILES = 512;
+constexpr int F32_BUF = 2 * (32 + 64) * 32;         // floats of one buffer: the 32-row shape's two slices
+
+template <int MODE, int BM, int KW>
+__device__ inline void f32_tiles(const GemmArgs& p, float* b0, float* b1, float* b2) {
+    constexpr int WPS = BM / 32 * 2;                // waves per K slice
+    constexpr int AV = BM / 8 / WPS, BV = F32_BN / 8 / WPS;   // 8-row load instructions per wave and step
+    constexpr int SLICE = (BM + F32_BN) * 32;       // floats of one K slice in a buffer
+    static_assert(WPS * KW == F32_THREADS / 64 && SLICE * KW <= F32_BUF, "four waves, one buffer");
+    static_assert(F32_THREADS / 64 * 16 * 64 <= F32_BUF, "the waves' sums fit a buffer");
+    constexpr uint32_t OOR = 0x80000000u;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = wave / WPS, ws = wave % WPS;     // K slice, wave inside it
+    const int wm = ws >> 1, wn = ws & 1;
+    const int grid = (int)gridDim.x;                // a multiple of 8
+    const int vid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
+    const int rsub = lane >> 3;
+    for (int tile = vid;; tile += grid) {
         TileLoc L;
-        if (!decode_tile<BM, BN>(p, tile, L)) break;
+        if (!decode_tile<BM, F32_BN>(p, tile, L)) break;
         const bool shared = L.g >= p.n_routed;
-        const float* Bw = shared ? (const float*)p.Ws : (const float*)p.Wr + (int64_t)L.g * L.N * L.K;
-        float acc[4][4] = {};
-        for (int k0 = 0; k0 < L.K; k0 += BK) {
-            // A tile: 64 rows x 16 k, B tile: 64 cols x 16 k (4 elements per thread each)
-            for (int v = 0; v < 4; ++v) {
-                const int id = v * 256 + tid, r = id >> 4, kk = id & 15;
-                const int row = L.m0 + r;
-                float av = 0.f;
-                if (row < L.R) {
-                    if (MODE == 0) {
-                        const int tok = p.row_tok[L.rowbase + row];
-                        av = ((const float*)p.X)[(int64_t)tok * p.ldx + k0 + kk];
-                    } else {
-                        const float* base = shared ? (const float*)p.As
-                                                   : (const float*)p.Ar + (int64_t)L.rowbase * L.K;
-                        av = base[(int64_t)row * L.K + k0 + kk];
-                    }
-                }
-                sA[kk][r] = av;
-                sB[kk][r] = Bw[(int64_t)(L.n0 + r) * L.K + k0 + kk];
-            }
-            __syncthreads();
+        const int K = L.K;
+        const float* Bw = shared ? (const float*)p.Ws : (const float*)p.Wr + (size_t)L.g * L.N * K;
+        const float* Ab = MODE == 0 ? (const float*)p.X
+                                    : (shared ? (const float*)p.As : (const float*)p.Ar + (size_t)L.rowbase * K);
+        const __amdgpu_buffer_rsrc_t rb_rs = make_rsrc(Bw, (uint32_t)((size_t)L.N * K * 4));
+        const __amdgpu_buffer_rsrc_t ra_rs = make_rsrc(Ab, MODE == 0 ? p.x_bytes : (uint32_t)((size_t)L.R * K * 4));
+        uint32_t aoff[AV], boff[BV];
 #pragma unroll
-            for (int kk = 0; kk < BK; ++kk) {
-                float a4[4], b4[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { a4[i] = sA[kk][ty * 4 + i]; b4[i] = sB[kk][tx * 4 + i]; }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a4[i], b4[j], acc[i][j]);
-            }
-            __syncthreads();
+        for (int v = 0; v < AV; ++v) {
+            const int r = (ws * AV + v) * 8 + rsub, row = L.m0 + r;
+            const uint32_t src = MODE == 0 ? (row < L.R ? (uint32_t)p.row_tok[L.rowbase + row] : 0u) : (uint32_t)row;
+            const uint32_t ch = (lane & 7) ^ ((r >> 1) & 7);
+            aoff[v] = row < L.R ? (src * (uint32_t)(MODE == 0 ? p.ldx : K) + ch * 4) * 4u : OOR;
         }
-        if (MODE == 1) {
-            float* out = (float*)p.Or;
-            for (int i = 0; i < 4; ++i) {
-                const int row = L.m0 + ty * 4 + i;
-                if (row >= L.R) continue;
-                const float wr = p.row_w[L.rowbase + row];
-                for (int j = 0; j < 4; ++j)
-                    out[(int64_t)(L.rowbase + row) * L.N + L.n0 + tx * 4 + j] = acc[i][j] * wr;
-            }
+#pragma unroll
+        for (int v = 0; v < BV; ++v) {
+            const int r = (ws * BV + v) * 8 + rsub;
+            const uint32_t ch = (lane & 7) ^ ((r >> 1) & 7);
+            boff[v] = ((uint32_t)(L.n0 + r) * (uint32_t)K + ch * 4) * 4u;
         }
-        if (MODE == 0) {
-            // packed rows alternate 16 gate / 16 up columns: pair them up
-            // through LDS, then write silu(g) * u
-            __shared__ float sC[BM][BN + 1];
-            for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) sC[ty * 4 + i][tx * 4 + j] = acc[i][j];
-            __syncthreads();
+        const int nslices = K / 32, nsteps = (nslices + KW - 1) / KW;
+        // the loads of this wave's share of K step st into buffer b (slices past K: zeros)
+        auto issue = [&](float* b, int st) {
+            const int sl = st * KW + ks;
+            const uint32_t past = sl < nslices ? 0u : OOR, so = sl < nslices ? (uint32_t)sl * 128u : 0u;
+            float* d = b + ks * SLICE;
+#pragma unroll
+            for (int v = 0; v < AV; ++v) {
+                const uint32_t vo = aoff[v] | past;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra_rs, (lds_ptr)(d + (ws * AV + v) * 8 * 32), 16, vo, so, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < BV; ++v) {
+                const uint32_t vo = boff[v] | past;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb_rs, (lds_ptr)(d + BM * 32 + (ws * BV + v) * 8 * 32), 16, vo,
+                                                         so, 0, 0);
+            }
+        };
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        const int fa = (wm * 32 + (lane & 31)) * 32, fb = (BM + wn * 32 + (lane & 31)) * 32;
+        auto mma = [&](const float* b) {
+            const float* d = b + ks * SLICE;
+            f32x4 av[4], bv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int ch = ((2 * q + (lane >> 5)) ^ ((lane >> 1) & 7)) * 4;   // row & 31 = lane & 31
+                av[q] = *(const f32x4*)(d + fa + ch);
+                bv[q] = *(const f32x4*)(d + fb + ch);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q][j], bv[q][j], acc, 0, 0, 0);
+        };
+        // step st: its loads have arrived (the younger step's may be in flight),
+        // every wave is past step st - 1, whose buffer takes the loads of st + 2
+        auto step = [&](float* cur, float* nxt, int st) {
+            __builtin_amdgcn_s_waitcnt(waitcnt_enc(AV + BV, 0));
+            lds_barrier();
+            issue(nxt, st + 2);
+            mma(cur);
+        };
+        issue(b0, 0);
+        issue(b1, 1);
+        int st = 0;
+        for (; st + 3 <= nsteps; st += 3) {
+            step(b0, b2, st);
+            step(b1, b0, st + 1);
+            step(b2, b1, st + 2);
+        }
+        if (st < nsteps) step(b0, b2, st);
+        if (st + 1 < nsteps) step(b1, b0, st + 1);
+        // loads past the last step may still be in flight into a buffer
+        __builtin_amdgcn_s_waitcnt(waitcnt_enc(0, 0));
+        lds_barrier();
+        float* red = b0;                            // [4 waves][16][64]
+#pragma unroll
+        for (int e = 0; e < 16; ++e) red[(wave * 16 + e) * 64 + lane] = acc[e];
+        __syncthreads();
+        // element e of lane l of a 32 x 32 block: row (e/4)*8 + (l/32)*4 + e%4, column l%32
+        auto sum = [&](int w, int e) {              // over the K slices, in order
+            float v = red[(w * 16 + e) * 64 + lane];
+#pragma unroll
+            for (int z = 1; z < KW; ++z) v += red[((z * WPS + w) * 16 + e) * 64 + lane];
+            return v;
+        };
+        if constexpr (MODE == 0) {
+            // block 0 holds 32 gate columns, block 1 the matching up columns
             float* out = shared ? (float*)p.Os : (float*)p.Or;
-            const int ldo = L.N / 2;
-            for (int idx = tid; idx < BM * (BN / 2); idx += 256) {
-                const int r = idx / (BN / 2), c = idx % (BN / 2);   // activation column within tile
-                const int row = L.m0 + r;
-                if (row >= L.R) continue;
-                const int blk = c >> 5, cc = c & 31;
-                const float gv = sC[r][blk * 64 + cc], uv = sC[r][blk * 64 + 32 + cc];
-                const int orow = (shared ? 0 : L.rowbase) + row;
-                out[(int64_t)orow * ldo + L.n0 / 2 + c] = gv / (1.0f + __expf(-gv)) * uv;   // fp32: IEEE divide
+            const int ldo = L.N / 2, orow0 = shared ? 0 : L.rowbase;
+            for (int i = wave; i < BM / 32 * 16; i += F32_THREADS / 64) {
+                const int m = i >> 4, e = i & 15;
+                const int row = L.m0 + m * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                const float gv = sum(2 * m, e), uv = sum(2 * m + 1, e);
+                if (row < L.R)
+                    out[(size_t)(orow0 + row) * ldo + L.n0 / 2 + (lane & 31)] =
+                        gv / (1.0f + __expf(-gv)) * uv;   // fp32: IEEE divide
             }
-            __syncthreads();
+        } else {
+            float* out = (float*)p.Or;
+            for (int i = wave; i < BM / 32 * 2 * 16; i += F32_THREADS / 64) {
+                const int w = i >> 4, e = i & 15;
+                const int row = L.m0 + (w >> 1) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                const float v = sum(w, e);
+                if (row < L.R)
+                    out[(size_t)(L.rowbase + row) * L.N + L.n0 + (w & 1) * 32 + (lane & 31)] =
+                        v * p.row_w[L.rowbase + row];
+            }
         }
+        __syncthreads();                            // before the next tile's loads overwrite the sums
     }
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(F32_THREADS) ggemm_f32(const GemmArgs p) {
+    __shared__ __attribute__((aligned(16))) float b0[F32_BUF], b1[F32_BUF], b2[F32_BUF];
+    // (the tile count is of 64-row tiles)
+    if (*p.ntiles >= F32_TALL_TILES) f32_tiles<MODE, F32_BM, 1>(p, b0, b1, b2);
+    else f32_tiles<MODE, 32, 2>(p, b0, b1, b2);
 }
 
 struct CombineArgs {
@@ -1252,7 +1335,6 @@ constexpr int GU_BM = 256, GU_BN = 256, DN_BM = 192, DN_BN = 256;   // bf16 GEMM
 // rows, which spread a few thousand rows over more of the 256 CUs.
 constexpr int DN_BM_TALL = 256;
 constexpr int64_t DN_TALL_ROUNDS = 8;
-constexpr int F32_BM = 64, F32_BN = 64;
 // bf16 batches of at most THIN_MAX_T tokens (every expert then has at most that
 // many rows) take the thin GEMM, THIN_PER_CU resident workgroups per CU
 constexpr int64_t THIN_MAX_T = 128;
@@ -1369,7 +1451,7 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     } else {
         {
         KernelTimer kt_("gemm_gate_up", st);
-        ggemm_f32<0><<<dim3(persistent_grid(ub_gu, 4)), dim3(256), 0, st>>>(g);
+        ggemm_f32<0><<<dim3(persistent_grid(2 * ub_gu, F32_PER_CU)), dim3(F32_THREADS), 0, st>>>(g);
         }
         if ((e = hipGetLastError()) != hipSuccess) return (int)e;
     }
@@ -1392,7 +1474,7 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     } else {
         {
         KernelTimer kt_("gemm_down", st);
-        ggemm_f32<1><<<dim3(persistent_grid(ub_dn, 4)), dim3(256), 0, st>>>(g);
+        ggemm_f32<1><<<dim3(persistent_grid(2 * ub_dn, F32_PER_CU)), dim3(F32_THREADS), 0, st>>>(g);
         }
     }
     if ((e = hipGetLastError()) != hipSuccess) return (int)e;
