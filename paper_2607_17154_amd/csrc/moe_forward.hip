@@ -428,28 +428,60 @@ struct TileLoc {
 
 // Tile order: the shared group first (its down projection has the longest K,
 // so its tiles start first and the shorter routed tiles fill in around them),
-// then the routed groups; inside a group tiles are m-fastest.
+// then the routed groups; inside a group tiles are m-fastest.  Lane g of a wave
+// holds routed group g: one read of the row offsets and one scan give every
+// group's first tile, and a ballot finds the group of a tile.  (A loop over the
+// groups waits for the reads of one group after the other: 4 us of a one-token
+// layer of 32 local experts, 3 us of the 8192-token Qwen-shaped layer.)
+struct GroupScan {
+    int off, R, cum;              // lane g: first row, rows and first tile of routed group g
+    int sh_off, sh_R, sh_cnt;     // shared group: first row, rows and tiles
+};
 template <int BM, int BN>
-__device__ inline bool decode_tile(const GemmArgs& p, int tile, TileLoc& L) {
-    int rem = tile;
-    const bool has_sh = p.G > p.n_routed;
-    for (int gi = 0; gi < p.G; ++gi) {
-        const int g = has_sh ? (gi == 0 ? p.n_routed : gi - 1) : gi;
-        const int off = p.offsets[g];
-        const int R = p.offsets[g + 1] - off;
-        const bool sh = g >= p.n_routed;
-        const int N = sh ? p.Ns : p.Nr;
-        const int mt = (R + BM - 1) / BM;
-        const int cnt = mt * (N / BN);
-        if (rem < cnt) {
-            L.g = g; L.R = R; L.N = N; L.K = sh ? p.Ks : p.Kr; L.rowbase = off;
-            L.m0 = (rem % mt) * BM;
-            L.n0 = (rem / mt) * BN;
-            return true;
-        }
-        rem -= cnt;
+__device__ inline GroupScan scan_groups(const GemmArgs& p, int lane) {
+    static_assert(ORDERMOE_MAX_LOCAL <= 64, "one routed group per lane");
+    const int n = p.n_routed;
+    GroupScan s;
+    const int o1 = p.offsets[lane < n ? lane + 1 : n];
+    s.off = p.offsets[lane < n ? lane : n];
+    s.R = o1 - s.off;             // lanes past the groups: none
+    s.sh_off = s.sh_R = s.sh_cnt = 0;
+    if (p.G > n) {
+        s.sh_off = p.offsets[n];
+        s.sh_R = p.offsets[n + 1] - s.sh_off;
+        s.sh_cnt = (s.sh_R + BM - 1) / BM * (p.Ns / BN);
     }
-    return false;
+    const int cnt = (s.R + BM - 1) / BM * (p.Nr / BN);
+    int inc = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(inc, o);
+        if (lane >= o) inc += v;
+    }
+    s.cum = inc - cnt;
+    return s;
+}
+template <int BM, int BN>
+__device__ inline bool find_tile(const GemmArgs& p, const GroupScan& s, int tile, int lane, TileLoc& L) {
+    int rem = tile;
+    if (tile < s.sh_cnt) {
+        L.g = p.n_routed; L.R = s.sh_R; L.N = p.Ns; L.K = p.Ks; L.rowbase = s.sh_off;
+    } else {
+        rem -= s.sh_cnt;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(lane < p.n_routed && s.cum <= rem);
+        if (!m) return false;
+        // the last group that starts at or before the tile (an empty group starts where the next one does)
+        const int g = 63 - __builtin_clzll(m);
+        L.g = g; L.N = p.Nr; L.K = p.Kr;
+        L.R = __builtin_amdgcn_readlane(s.R, g);
+        L.rowbase = __builtin_amdgcn_readlane(s.off, g);
+        rem -= __builtin_amdgcn_readlane(s.cum, g);
+    }
+    const int mt = (L.R + BM - 1) / BM;
+    if (rem >= mt * (L.N / BN)) return false;
+    L.m0 = (rem % mt) * BM;
+    L.n0 = (rem / mt) * BN;
+    return true;
 }
 
 // Position of workgroup vid in round r of n work items (n <= grid): odd
@@ -488,14 +520,16 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
 constexpr int BUF_DWORD3 = 0x00020000;   // raw buffer resource word 3 on gfx9-class GPUs
+constexpr int NT = 2;                    // buffer load/store cache bit nt: non-temporal
 constexpr int SC1 = 16;                  // buffer load/store cache bit sc1: coherent at agent scope
 
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, BUF_DWORD3);
 }
 
+template <int AUX = 0>
 __device__ inline bf16x8 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
+    u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, AUX);
     return __builtin_bit_cast(bf16x8, v);
 }
 
@@ -615,6 +649,8 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
         // the wave index as a scalar: the LDS destinations of the loads into LDS
         // (the M0 operand) are then scalar expressions, not VGPRs held per buffer
         const int wave_u = __builtin_amdgcn_readfirstlane(wave_r);
+        // (scanned per tile: held across the K loop it would spill)
+        const GroupScan gs = scan_groups<BM, BN>(p, lane_r);
         TileLoc L;
         int kt_lo = 0, kt_hi = 0;       // K tiles of 64 of this piece
         int nseg = 1, ctr = 0, pslot = 0;
@@ -631,13 +667,13 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
                 const int j = item / nsh;
                 ctr = item - j * nsh;
                 pslot = item;
-                if (!decode_tile<BM, BN>(p, ctr, L)) break;
+                if (!find_tile<BM, BN>(p, gs, ctr, lane_r, L)) break;
                 const int half = L.K / (2 * BK);          // even: K is a multiple of 4 BK
                 kt_lo = j * half;
                 kt_hi = kt_lo + half;
                 nseg = 2;
             } else {
-                if (!decode_tile<BM, BN>(p, sh_split ? item - nsh : item, L)) break;
+                if (!find_tile<BM, BN>(p, gs, sh_split ? item - nsh : item, lane_r, L)) break;
                 kt_hi = L.K / BK;
             }
         } else {
@@ -646,7 +682,7 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
             const int j = pos / left;
             ctr = pos - j * left;
             pslot = pos;
-            if (!decode_tile<BM, BN>(p, head + ctr, L)) break;
+            if (!find_tile<BM, BN>(p, gs, head + ctr, lane_r, L)) break;
             const int units = L.K / (2 * BK);
             kt_lo = 2 * (j * units / split);
             kt_hi = 2 * ((j + 1) * units / split);
@@ -976,7 +1012,12 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
 // memory straight into MFMA registers.  Two register sets keep the next step's
 // reads in flight during the current step.  The waves' partial sums meet in LDS
 // and are added in wave order, then the epilogue of ggemm_bf16 runs on the
-// sums.
+// sums.  The weights of an expert of at most 32 rows are read exactly once, as
+// non-temporal loads: those stream at 7.0 TB/s here, ordinary ones at 6.2 (64
+// tokens, 30 experts of d = 4096, f = 1536: layer 245 -> 225 us; one token 58 ->
+// 55 us).  With more row tiles the tiles after the first find the weights in
+// L2, which non-temporal loads would forfeit (2 x 35 rows of d = 4096,
+// f = 14336: 205 -> 231 us), so those keep ordinary loads.
 constexpr int TH_BM = 32, TH_BN = 64, TH_WAVES = 4;
 constexpr int TH_LDK = 144;                        // bytes per staged weight row
 constexpr int TH_LDS = TH_WAVES * TH_BN * TH_LDK;  // staging; reused for the partial sums
@@ -998,13 +1039,14 @@ ggemm_thin(const GemmArgs p) {
     // rounds of gridDim.x tiles; the last, partial round shared evenly by the
     // XCDs when every tile has the same K
     const bool spread = !(p.G > p.n_routed && p.Ks != p.Kr);
+    const GroupScan gs = scan_groups<TH_BM, TH_BN>(p, lane);
     for (int r = 0; r * (int)gridDim.x < total; ++r) {
         const int n = total - r * (int)gridDim.x;
         const int pos = round_pos(vid, 0, n, (int)gridDim.x, spread);
         if (pos < 0) break;
         const int tile = r * (int)gridDim.x + pos;
         TileLoc L;
-        if (!decode_tile<TH_BM, TH_BN>(p, tile, L)) break;
+        if (!find_tile<TH_BM, TH_BN>(p, gs, tile, lane, L)) break;
         const bool shared = L.g >= p.n_routed;
         const int K = L.K;
         const __bf16* Bw = shared ? (const __bf16*)p.Ws
@@ -1036,14 +1078,17 @@ ggemm_thin(const GemmArgs p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) { acc0[e] = 0.f; acc1[e] = 0.f; }
         bf16x8 w[2][8], a[2][4];
-        auto load = [&](int buf, int it) {
+        // weights that one row tile reads are read once: non-temporal
+        const bool once = L.R <= TH_BM;
+        auto load = [&](auto nt, int buf, int it) {
+            constexpr int AUX = decltype(nt)::value;
             const int st = wave + it * TH_WAVES;
             // a step past the end reads zeros through the range check and adds nothing
             const uint32_t ok = it < nst ? 0u : OOR;
             const uint32_t k0 = (uint32_t)st * 128u;   // bytes into a token or activation row
             const uint32_t kb = (uint32_t)st * (uint32_t)(WB_ROWS * WB_K * 2);   // bytes into the weight blocks
 #pragma unroll
-            for (int i = 0; i < 8; ++i) w[buf][i] = buf_load16(rb_rs, (wblk0 + i * 1024u) | ok, kb);
+            for (int i = 0; i < 8; ++i) w[buf][i] = buf_load16<AUX>(rb_rs, (wblk0 + i * 1024u) | ok, kb);
 #pragma unroll
             for (int i = 0; i < 4; ++i) a[buf][i] = buf_load16(ra_rs, aoff | ok, k0 + 32u * i);
         };
@@ -1063,17 +1108,21 @@ ggemm_thin(const GemmArgs p) {
                 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[buf][i], b1[i], acc1, 0, 0, 0);
             }
         };
-        load(0, 0);
-        for (int it = 0; it < nst; it += 2) {
-            load(1, it + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(0);
-            __builtin_amdgcn_sched_barrier(0);
-            load(0, it + 2);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        auto kloop = [&](auto nt) __attribute__((always_inline)) {
+            load(nt, 0, 0);
+            for (int it = 0; it < nst; it += 2) {
+                load(nt, 1, it + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                mma(0);
+                __builtin_amdgcn_sched_barrier(0);
+                load(nt, 0, it + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                mma(1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (once) kloop(std::integral_constant<int, NT>{});
+        else kloop(std::integral_constant<int, 0>{});
         __syncthreads();     // every wave is done with its staging rows
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -1157,9 +1206,10 @@ __device__ inline void f32_tiles(const GemmArgs& p, float* b0, float* b1, float*
     const int grid = (int)gridDim.x;                // a multiple of 8
     const int vid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
     const int rsub = lane >> 3;
+    const GroupScan gs = scan_groups<BM, F32_BN>(p, lane);
     for (int tile = vid;; tile += grid) {
         TileLoc L;
-        if (!decode_tile<BM, F32_BN>(p, tile, L)) break;
+        if (!find_tile<BM, F32_BN>(p, gs, tile, lane, L)) break;
         const bool shared = L.g >= p.n_routed;
         const int K = L.K;
         const float* Bw = shared ? (const float*)p.Ws : (const float*)p.Wr + (size_t)L.g * L.N * K;
