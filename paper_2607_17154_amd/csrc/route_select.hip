@@ -32,6 +32,7 @@
 #include <cstdint>
 
 #include "common.hpp"
+#include "logits_f64.hpp"
 
 namespace ordermoe {
 namespace {
@@ -306,100 +307,13 @@ __device__ inline void router_lds_loop(const RouteArgs& a, int kw, int lane, int
     }
 }
 
-// fp32 storage: the router logits of a 16-token block by
-// v_mfma_f64_16x16x4_f64.  The 8 waves take the 16-expert blocks (NBT of them,
-// a power of two) and, with fewer than 8 blocks, KW slices of the K steps of
-// 16; the slices' fp64 sums meet in LDS and are added in slice order, then
-// rounded once to fp32.  A lane reads four consecutive K values of its token
-// row and of its expert row (16 bytes each) and feeds them to four MFMAs, so K
-// runs in the order 0, 4, 8, 12, 1, 5, ... of each step.  Rows past the batch
-// and experts past E re-read the last one; their logits are never used.  A
-// thread per logit with a serial fp64 chain over d took 312 us (1001 tokens,
-// d = 1024, 40 experts) and 47 us (256 tokens, d = 512, 8 experts) for the
-// whole kernel; now 24 and 11 us.
-template <int NBT>
-__device__ inline void router_f64(const RouteArgs& a, int wave, int lane, int tid, int64_t t0, float* s_logit) {
-    typedef double f64x4 __attribute__((ext_vector_type(4)));
-    constexpr int EG = NBT < RT_WAVES ? NBT : RT_WAVES;      // expert groups
-    constexpr int KW = RT_WAVES / EG;                        // K slices
-    constexpr int NB = NBT / EG;                             // 16-expert blocks per wave
-    constexpr int U = 4;                                     // K steps per set of reads
-    const int d = a.d, E = a.E, Epad = (E + 15) & ~15;
-    const int eg = wave / KW, kw = wave % KW;
-    const int r16 = lane & 15, kq = (lane >> 4) * 4;
-    const int64_t tok = t0 + r16 < a.T ? t0 + r16 : a.T - 1;
-    const float* xr = (const float*)a.x + tok * (int64_t)d + kq;
-    const float* wr[NB];
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        const int e = (eg * NB + n) * 16 + r16;
-        wr[n] = (const float*)a.w_router + (int64_t)(e < E ? e : E - 1) * d + kq;
-    }
-    const int nsteps = d / 16;
-    const int ns = (nsteps - kw + KW - 1) / KW;              // steps of this wave
-    f64x4 acc[NB];
-#pragma unroll
-    for (int n = 0; n < NB; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
-    f32x4 xv[2][U], wv[2][U][NB];
-    auto load = [&](int b, int i0) {                         // (past the end: the last step, not multiplied)
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t o = (int64_t)(kw + KW * (i0 + u < ns ? i0 + u : ns - 1)) * 16;
-            xv[b][u] = *(const f32x4*)(xr + o);
-#pragma unroll
-            for (int n = 0; n < NB; ++n) wv[b][u][n] = *(const f32x4*)(wr[n] + o);
-        }
-    };
-    auto mma = [&](int b, int i0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (i0 + u < ns)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int n = 0; n < NB; ++n)
-                        acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xv[b][u][q], (double)wv[b][u][n][q],
-                                                                      acc[n], 0, 0, 0);
-    };
-    if (ns > 0) {
-        load(0, 0);
-        for (int i = 0; i < ns; i += 2 * U) {
-            load(1, i + U);
-            mma(0, i);
-            load(0, i + 2 * U);
-            mma(1, i + U);
-        }
-    }
-    // acc[n][i]: token 4 i + lane / 16, expert lane % 16 of the block
-    if constexpr (KW == 1) {
-#pragma unroll
-        for (int n = 0; n < NB; ++n) {
-            const int e = (eg * NB + n) * 16 + r16;
-            if (e < Epad)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) s_logit[(4 * i + (lane >> 4)) * Epad + e] = (float)acc[n][i];
-        }
-    } else {
-        double* part = (double*)(s_logit + RT_TB * Epad);    // [RT_WAVES][16][16]
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part[wave * 256 + (4 * i + (lane >> 4)) * 16 + r16] = acc[0][i];
-        __syncthreads();
-        for (int p = tid; p < RT_TB * Epad; p += RT_THREADS) {
-            const int tr = p / Epad, e = p - tr * Epad;
-            const double* q = part + (e >> 4) * KW * 256 + tr * 16 + (e & 15);
-            double v = q[0];
-#pragma unroll
-            for (int w = 1; w < KW; ++w) v += q[w * 256];
-            s_logit[p] = (float)v;
-        }
-    }
-}
-
-// LDS bytes of the fp32 router: the logits and, below 8 expert blocks, the fp64
-// partial sums of the 8 waves
+// LDS bytes of the fp32 router: the logits, then the fp64 sums of its K slices
+// (1001 tokens, d = 1024, 40 experts: 312 us for the kernel with a thread per
+// logit, 24 us now; 256 tokens, d = 512, 8 experts: 47 and 11 us)
+static_assert(RT_TB == LF_TOKENS && RT_THREADS == LF_THREADS, "one block of logits_f64");
 __host__ __device__ inline int route_f32_bytes(int E) {
     const int Epad = (E + 15) & ~15;
-    return RT_TB * Epad * 4 + (Epad <= 64 ? RT_WAVES * 256 * 8 : 0);
+    return RT_TB * Epad * 4 + logits_f64_part_bytes(Epad);
 }
 
 // One candidate table (T1 experts, T1 losses, T1 lengths, server masks, or the
@@ -637,7 +551,9 @@ route_select_kernel(const RouteArgs a) {
             s_logit[i] = v;
         }
     } else {
-        if constexpr (TB == RT_TB) router_f64<NBT>(a, wave, lane, tid, t0, s_logit);
+        if constexpr (TB == RT_TB)
+            logits_f64<NBT>((const float*)a.x, a.T, (const float*)a.w_router, E, d, t0, tid, s_logit, Epad,
+                            (double*)(s_logit + RT_TB * Epad));
     }
     {
         // second batches of the larger tables, read together

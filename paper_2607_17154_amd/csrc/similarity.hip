@@ -11,8 +11,10 @@
 //                        counts (and top-1), then Gram += H^T H by bf16 MFMAs
 //                        on a two-term bf16 split of H; per-workgroup partial
 //                        Gram and counts to the workspace
-//   sim_partial_kernel   fp32 storage: chunks of 128 tokens, fp64 dot products
-//                        rounded to fp32, same partial outputs
+//   sim_partial_kernel   bf16 with d not a multiple of 256: chunks of 128 tokens,
+//                        same partial outputs
+//   sim_f32_kernel       fp32 storage: chunks of 16 tokens, fp64 dot products
+//                        (matrix unit) rounded to fp32, same partial outputs
 //   sim_reduce_kernel    fixed-order fp64 sum of the partials: 16 slices of
 //                        parts per entry, then the slices in order
 //   sim_normalise_kernel cosine (eq 4)
@@ -22,6 +24,7 @@
 #include <cstdint>
 
 #include "common.hpp"
+#include "logits_f64.hpp"
 
 namespace ordermoe {
 namespace {
@@ -375,89 +378,71 @@ __global__ void __launch_bounds__(256) sim_partial_kernel(const SimArgs a) {
 
     for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
         const int64_t t0 = (int64_t)ch * SIM_TC;
-        if (a.dtype == ORDERMOE_BF16) {
-            const __bf16* X = (const __bf16*)a.x_cal;
-            const __bf16* W = (const __bf16*)a.w_router;
-            const int wm = wave >> 1, wn = wave & 1;       // 64 experts x 64 tokens per wave
-            const int r16 = lane & 15, kg = (lane >> 4) * 8;
-            const bf16x8 zero8 = {};
-            const __bf16* wp[4];
-            bool wok[4];
-            const __bf16* xp[4];
-            bool xok[4];
+        const __bf16* X = (const __bf16*)a.x_cal;
+        const __bf16* W = (const __bf16*)a.w_router;
+        const int wm = wave >> 1, wn = wave & 1;       // 64 experts x 64 tokens per wave
+        const int r16 = lane & 15, kg = (lane >> 4) * 8;
+        const bf16x8 zero8 = {};
+        const __bf16* wp[4];
+        bool wok[4];
+        const __bf16* xp[4];
+        bool xok[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = wm * 64 + i * 16 + r16;
-                wok[i] = e < E;
-                wp[i] = W + (int64_t)(wok[i] ? e : 0) * d + kg;
-                const int64_t t = t0 + wn * 64 + i * 16 + r16;
-                xok[i] = t < a.T_cal;
-                xp[i] = X + (xok[i] ? t : 0) * (int64_t)d + kg;
-            }
-            f32x4 acc[4][4];
+        for (int i = 0; i < 4; ++i) {
+            const int e = wm * 64 + i * 16 + r16;
+            wok[i] = e < E;
+            wp[i] = W + (int64_t)(wok[i] ? e : 0) * d + kg;
+            const int64_t t = t0 + wn * 64 + i * 16 + r16;
+            xok[i] = t < a.T_cal;
+            xp[i] = X + (xok[i] ? t : 0) * (int64_t)d + kg;
+        }
+        f32x4 acc[4][4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            // U K-steps of loads are issued before they are multiplied, so each
-            // wave keeps 8 * U loads of 16 bytes in flight (d % 64 == 0)
-            constexpr int U = 4;
-            int kk = 0;
-            for (; kk + 32 * U <= d; kk += 32 * U) {
-                bf16x8 av[U][4], bv[U][4];
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // U K-steps of loads are issued before they are multiplied, so each
+        // wave keeps 8 * U loads of 16 bytes in flight (d % 64 == 0)
+        constexpr int U = 4;
+        int kk = 0;
+        for (; kk + 32 * U <= d; kk += 32 * U) {
+            bf16x8 av[U][4], bv[U][4];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        av[u][i] = wok[i] ? *(const bf16x8*)(wp[i] + kk + 32 * u) : zero8;
-                        bv[u][i] = xok[i] ? *(const bf16x8*)(xp[i] + kk + 32 * u) : zero8;
-                    }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][i], bv[u][j], acc[i][j], 0, 0, 0);
-            }
-            for (; kk < d; kk += 32) {
-                bf16x8 av[4], bv[4];
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    av[i] = wok[i] ? *(const bf16x8*)(wp[i] + kk) : zero8;
-                    bv[i] = xok[i] ? *(const bf16x8*)(xp[i] + kk) : zero8;
+                    av[u][i] = wok[i] ? *(const bf16x8*)(wp[i] + kk + 32 * u) : zero8;
+                    bv[u][i] = xok[i] ? *(const bf16x8*)(xp[i] + kk + 32 * u) : zero8;
                 }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][i], bv[u][j], acc[i][j], 0, 0, 0);
+        }
+        for (; kk < d; kk += 32) {
+            bf16x8 av[4], bv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                av[i] = wok[i] ? *(const bf16x8*)(wp[i] + kk) : zero8;
+                bv[i] = xok[i] ? *(const bf16x8*)(xp[i] + kk) : zero8;
             }
-            // acc[i][j][q]: expert wm*64 + i*16 + (lane/16)*4 + q, token wn*64 + j*16 + lane%16
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        s_H[wm * 64 + i * 16 + (lane >> 4) * 4 + q][wn * 64 + j * 16 + r16] = acc[i][j][q];
-        } else {
-            const float* X = (const float*)a.x_cal;
-            const float* W = (const float*)a.w_router;
-            for (int p = tid; p < SIM_EMAX * SIM_TC; p += 256) {
-                const int e = p / SIM_TC, tt = p % SIM_TC;
-                const int64_t t = t0 + tt;
-                float v = 0.f;
-                if (e < E && t < a.T_cal) {
-                    const float* xr = X + t * (int64_t)d;
-                    const float* wr = W + (int64_t)e * d;
-                    double s = 0.0;
-                    for (int i = 0; i < d; ++i) s = fma((double)xr[i], (double)wr[i], s);
-                    v = (float)s;
-                }
-                s_H[e][tt] = v;
-            }
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
         }
+        // acc[i][j][q]: expert wm*64 + i*16 + (lane/16)*4 + q, token wn*64 + j*16 + lane%16
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    s_H[wm * 64 + i * 16 + (lane >> 4) * 4 + q][wn * 64 + j * 16 + r16] = acc[i][j][q];
         __syncthreads();
 
         // activation counts: top-k of each token's logits, ties to the lower
@@ -517,25 +502,112 @@ __global__ void __launch_bounds__(256) sim_partial_kernel(const SimArgs a) {
     for (int i = tid; i < SIM_EMAX; i += 256) a.count_part[(int64_t)blockIdx.x * SIM_EMAX + i] = s_cnt[i];
 }
 
-// Fixed-order fp64 sum of the per-block partial Gram matrices and counts.
-// A block of 1024 threads takes 64 consecutive entries; thread (s, c) adds the
+// fp32 storage.  A block takes chunks of 16 tokens: their logits from
+// logits_f64 into LDS, then on the same tile the per-token top-k (waves 0 .. 3,
+// 16 lanes per token) and the Gram update, fp32 FMAs in token order with SE * SE
+// entries spread over the threads (SE: experts rounded up to a power of two, at
+// least 16).  A partial holds SE x SE floats, so that few experts leave room in
+// the workspace for one partial per SE tokens: 128 blocks for 2048 tokens of 8
+// experts, where chunks of 128 tokens gave 16 blocks with a serial fp64 chain
+// per logit (272 us; now 8.5 us).
+template <int SE>
+__global__ void __launch_bounds__(LF_THREADS) sim_f32_kernel(const SimArgs a) {
+    constexpr int LD = SE + 4;
+    constexpr int RI = SE >= 128 ? 4 : SE >= 64 ? 2 : 1, RJ = SE >= 128 ? 8 : SE >= 64 ? 4 : SE >= 32 ? 2 : 1;
+    constexpr int TJ = SE / RJ;                             // threads along a Gram row
+    __shared__ __attribute__((aligned(16))) float s_H[LF_TOKENS * LD];
+    __shared__ double s_part[SE <= 64 ? LF_WAVES * 256 : 1];
+    __shared__ int s_cnt[SE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int E = a.E;
+    const int nchunks = (int)((a.T_cal + LF_TOKENS - 1) / LF_TOKENS);
+    for (int i = tid; i < SE; i += LF_THREADS) s_cnt[i] = 0;
+    const int ti = tid / TJ * RI, tj = tid % TJ * RJ;       // this thread's Gram entries
+    const bool own = ti < SE;
+    float g[RI][RJ];
+#pragma unroll
+    for (int u = 0; u < RI; ++u)
+#pragma unroll
+        for (int v = 0; v < RJ; ++v) g[u][v] = 0.f;
+    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+        const int64_t t0 = (int64_t)ch * LF_TOKENS;
+        const int nt = (int)(a.T_cal - t0 < LF_TOKENS ? a.T_cal - t0 : LF_TOKENS);
+        logits_f64<SE / 16>((const float*)a.x_cal, a.T_cal, (const float*)a.w_router, E, a.d, t0, tid, s_H, LD, s_part);
+        __syncthreads();
+        // activation counts: top-k of each token's logits, ties to the lower index
+        if (wave < LF_TOKENS / 4) {
+            const int j16 = lane & 15, tt = wave * 4 + (lane >> 4);
+            const bool tok = tt < nt;
+            uint32_t removed = 0;
+            for (int r = 0; r < a.k; ++r) {
+                uint64_t best = 0;
+                for (int i = 0, e = j16; e < E; ++i, e += 16) {
+                    if (removed & (1u << i)) continue;
+                    const uint32_t u = __float_as_uint(s_H[tt * LD + e]);
+                    const uint32_t o = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+                    const uint64_t key = ((uint64_t)o << 32) | (uint32_t)(0xFFFFu - (uint32_t)e);
+                    best = key > best ? key : best;
+                }
+#pragma unroll
+                for (int off = 8; off >= 1; off >>= 1) {
+                    uint32_t lo = (uint32_t)best, hi = (uint32_t)(best >> 32);
+                    lo = __shfl_xor(lo, off, 16);
+                    hi = __shfl_xor(hi, off, 16);
+                    const uint64_t o = ((uint64_t)hi << 32) | lo;
+                    best = o > best ? o : best;
+                }
+                const int e = (int)(0xFFFFu - (uint32_t)(best & 0xFFFFu));
+                if (r == 0 && j16 == 0 && tok && a.top1) a.top1[t0 + tt] = e;
+                if ((e & 15) == j16) {
+                    removed |= 1u << (e >> 4);
+                    if (tok) atomicAdd(&s_cnt[e], 1);
+                }
+            }
+        }
+        // Gram of this chunk (entries past E mean nothing and are not read)
+        if (own)
+            for (int t = 0; t < nt; ++t) {
+                float hu[RI], hv[RJ];
+#pragma unroll
+                for (int u = 0; u < RI; ++u) hu[u] = s_H[t * LD + ti + u];
+#pragma unroll
+                for (int v = 0; v < RJ; ++v) hv[v] = s_H[t * LD + tj + v];
+#pragma unroll
+                for (int u = 0; u < RI; ++u)
+#pragma unroll
+                    for (int v = 0; v < RJ; ++v) g[u][v] = fmaf(hu[u], hv[v], g[u][v]);
+            }
+        __syncthreads();
+    }
+    if (own) {
+        float* gp = a.gram_part + (int64_t)blockIdx.x * SE * SE;
+#pragma unroll
+        for (int u = 0; u < RI; ++u)
+#pragma unroll
+            for (int v = 0; v < RJ; ++v) gp[(ti + u) * SE + tj + v] = g[u][v];
+    }
+    for (int i = tid; i < SE; i += LF_THREADS) a.count_part[(int64_t)blockIdx.x * SE + i] = s_cnt[i];
+}
+
+// Fixed-order fp64 sum of the per-block partial Gram matrices (se x se floats
+// each) and counts.  A block of 1024 threads takes 64 consecutive entries; thread (s, c) adds the
 // parts s, s + 16, ... of entry c (independent loads, coalesced over c), then
 // the 16 slices are added in slice order.
 constexpr int RED_SLICES = 16, RED_COLS = 64;
 
-__global__ void __launch_bounds__(RED_SLICES * RED_COLS) sim_reduce_kernel(const SimArgs a, int nparts,
+__global__ void __launch_bounds__(RED_SLICES * RED_COLS) sim_reduce_kernel(const SimArgs a, int nparts, int se,
                                                                            double* gram) {
     __shared__ double s_g[RED_SLICES][RED_COLS];
     __shared__ int64_t s_c[RED_SLICES][RED_COLS];
     const int c = threadIdx.x % RED_COLS, sl = threadIdx.x / RED_COLS;
-    const int p = blockIdx.x * RED_COLS + c;            // entry of the 128 x 128 Gram
+    const int p = blockIdx.x * RED_COLS + c;            // entry of the se x se Gram
     double g = 0.0;
     int64_t n = 0;
     const float* src = a.gram_part + p;
 #pragma unroll 4
-    for (int b = sl; b < nparts; b += RED_SLICES) g += (double)src[(int64_t)b * SIM_EMAX * SIM_EMAX];
-    if (p < SIM_EMAX)
-        for (int b = sl; b < nparts; b += RED_SLICES) n += a.count_part[(int64_t)b * SIM_EMAX + p];
+    for (int b = sl; b < nparts; b += RED_SLICES) g += (double)src[(int64_t)b * se * se];
+    if (p < se)
+        for (int b = sl; b < nparts; b += RED_SLICES) n += a.count_part[(int64_t)b * se + p];
     s_g[sl][c] = g;
     s_c[sl][c] = n;
     __syncthreads();
@@ -543,7 +615,7 @@ __global__ void __launch_bounds__(RED_SLICES * RED_COLS) sim_reduce_kernel(const
         double t = 0.0;
         int64_t m = 0;
         for (int q = 0; q < RED_SLICES; ++q) { t += s_g[q][c]; m += s_c[q][c]; }
-        gram[p] = t;
+        gram[p / se * SIM_EMAX + p % se] = t;
         if (p < a.E) a.counts[p] = m;
     }
 }
@@ -570,9 +642,20 @@ int similarity_max_experts() { return SIM_EMAX; }
 
 int launch_similarity(const SimArgs& a, void* stream) {
     hipStream_t st = (hipStream_t)stream;
-    int nparts = a.nchunk;
+    int nparts = a.nchunk, se = SIM_EMAX;
     hipError_t e;
-    if (a.dtype == ORDERMOE_BF16 && a.d % (ST_BK * ST_STAGES) == 0) {
+    if (a.dtype == ORDERMOE_F32) {
+        // one partial per se tokens fits the workspace's slots of 128 tokens
+        while (se > 16 && se / 2 >= a.E) se /= 2;
+        const int64_t nch = (a.T_cal + LF_TOKENS - 1) / LF_TOKENS, slots = (int64_t)a.nchunk * (SIM_EMAX / se);
+        nparts = (int)(nch < slots ? nch : slots);
+        KernelTimer kt_("sim_partial", st);
+        const dim3 gr(nparts), bl(LF_THREADS);
+        if (se == 16) sim_f32_kernel<16><<<gr, bl, 0, st>>>(a);
+        else if (se == 32) sim_f32_kernel<32><<<gr, bl, 0, st>>>(a);
+        else if (se == 64) sim_f32_kernel<64><<<gr, bl, 0, st>>>(a);
+        else sim_f32_kernel<128><<<gr, bl, 0, st>>>(a);
+    } else if (a.dtype == ORDERMOE_BF16 && a.d % (ST_BK * ST_STAGES) == 0) {
         static int lds_ok = -1;
         if (lds_ok < 0)
             lds_ok = (int)hipFuncSetAttribute((const void*)sim_tile_kernel,
@@ -591,8 +674,8 @@ int launch_similarity(const SimArgs& a, void* stream) {
     if (e != hipSuccess) return (int)e;
     {
         KernelTimer kt_("sim_reduce", st);
-        hipLaunchKernelGGL(sim_reduce_kernel, dim3(SIM_EMAX * SIM_EMAX / RED_COLS), dim3(RED_SLICES * RED_COLS),
-                           0, st, a, nparts, a.gram);
+        hipLaunchKernelGGL(sim_reduce_kernel, dim3(se * se / RED_COLS), dim3(RED_SLICES * RED_COLS),
+                           0, st, a, nparts, se, a.gram);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

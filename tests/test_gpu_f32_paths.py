@@ -103,3 +103,32 @@ def test_f32_forward_at_the_tile_edges(rows, d, f, n_shared):
     print("rows %s d %d f %d: max err %.3g of the largest output (bound %.3g)" % (rows, d, f, err, bound), flush=True)
     assert err <= bound
     assert ro.cpu().tolist()[:n] == list(np.concatenate([[0], np.cumsum(rows)[:-1]]))
+
+
+@pytest.mark.parametrize("E,T", [(1, 1), (8, 2048), (16, 129), (17, 1000), (33, 15), (64, 700), (65, 257), (128, 1041)])
+def test_f32_similarity_at_the_partial_edges(E, T):
+    """The fp32 similarity build at the edges of its partial sizes (16, 32, 64,
+    128 experts) and chunks of 16 tokens.  A Gram entry sums at most 128 fp32
+    products per partial before fp64 takes over: each addition rounds by
+    2^-24 of a partial that is at most |h_i||h_j|, so a cosine is off by at most
+    128 x 2^-24 and a little from the rounded logits."""
+    from oracle import similarity as osim
+    rng = np.random.default_rng(E * 7 + T)
+    d, k = 192, min(E, 4)
+    x = rng.standard_normal((T, d), dtype=np.float32)
+    w = (rng.standard_normal((E, d)) * d ** -0.5).astype(np.float32)
+    ws = torch.empty(om.ordermoe_similarity_workspace_size(T, d, E), dtype=torch.uint8, device="cuda")
+    top1 = torch.empty(T, dtype=torch.int32, device="cuda")
+    got = om.ordermoe_build_similarity(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), k, 0.7, 0.5, ws, top1=top1)
+    H = osim.logit_matrix(x, w)                                   # [E][T]
+    gram = H @ H.T
+    n = np.sqrt(np.diag(gram))
+    want = gram / np.outer(n, n)
+    np.fill_diagonal(want, 1.0)
+    assert np.max(np.abs(got["sim"] - want)) <= 130 * 2.0 ** -24
+    # no ties within rounding in these draws except by chance: count them out
+    idx, srt = oroute.topk(H.T, k)
+    near = int(np.sum(oroute.margin(srt) < 1e-6)) if E > 1 else 0
+    counts = np.bincount(idx.ravel(), minlength=E)
+    assert np.abs(got["counts"] - counts).sum() <= 2 * near
+    assert int(np.sum(top1.cpu().numpy() != idx[:, 0])) <= near
