@@ -46,7 +46,13 @@ static size_t sim_ws(int64_t T_cal, Carver& c, SimArgs* a) {
     float* g = c.take<float>((size_t)parts * emax * emax);
     int32_t* n = c.take<int32_t>((size_t)parts * emax);
     double* gr = c.take<double>((size_t)emax * emax);
-    if (a) { a->gram_part = g; a->count_part = n; a->gram = gr; a->nchunk = parts; }
+    if (a) {
+        a->gram_part = g; a->count_part = n; a->gram = gr; a->nchunk = parts;
+        // the partials are done with when the outputs are staged; one partial's
+        // slot (at most 128 tokens) is too small for 128 experts' counts as well,
+        // and what follows it is still read
+        a->stage = parts >= 2 ? g : nullptr;
+    }
     return c.size();
 }
 
@@ -87,17 +93,24 @@ extern "C" int ordermoe_build_similarity(const void* x_cal, int64_t T_cal, int32
     int e = launch_similarity(a, stream);
     if (e) return hip_fail(e, "build_similarity launch");
 
-    std::vector<float> sim((size_t)E * E);
-    std::vector<int64_t> cnt(E);
+    // similarities and counts in one copy where they are staged side by side (a
+    // second copy of pageable memory costs 10 to 20 us)
+    const size_t nsim = (size_t)similarity_stage_counts(E), bytes = nsim * 4 + (size_t)E * 8;
+    std::vector<int64_t> host((bytes + 7) / 8);
     hipStream_t st = (hipStream_t)stream;
-    if ((e = (int)hipMemcpyAsync(sim.data(), sim_dev, sim.size() * 4, hipMemcpyDeviceToHost, st)))
-        return hip_fail(e, "build_similarity copy");
-    if ((e = (int)hipMemcpyAsync(cnt.data(), counts_dev, cnt.size() * 8, hipMemcpyDeviceToHost, st)))
-        return hip_fail(e, "build_similarity copy");
+    if (a.stage) {
+        e = (int)hipMemcpyAsync(host.data(), a.stage, bytes, hipMemcpyDeviceToHost, st);
+    } else {
+        e = (int)hipMemcpyAsync(host.data(), sim_dev, (size_t)E * E * 4, hipMemcpyDeviceToHost, st);
+        if (!e) e = (int)hipMemcpyAsync(host.data() + nsim / 2, counts_dev, (size_t)E * 8, hipMemcpyDeviceToHost, st);
+    }
+    if (e) return hip_fail(e, "build_similarity copy");
     if ((e = (int)hipStreamSynchronize(st))) return hip_fail(e, "build_similarity sync");
-    if (sim_host) std::copy(sim.begin(), sim.end(), sim_host);
-    if (counts_host) std::copy(cnt.begin(), cnt.end(), counts_host);
-    return ordermoe_group_experts(E, sim.data(), cnt.data(), theta, alpha_f, group_of, centres,
+    const float* sim = reinterpret_cast<const float*>(host.data());
+    const int64_t* cnt = host.data() + nsim / 2;
+    if (sim_host) std::copy(sim, sim + (size_t)E * E, sim_host);
+    if (counts_host) std::copy(cnt, cnt + E, counts_host);
+    return ordermoe_group_experts(E, sim, cnt, theta, alpha_f, group_of, centres,
                                   num_groups, importance);
 }
 

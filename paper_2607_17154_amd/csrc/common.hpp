@@ -123,11 +123,13 @@ struct SimArgs {
     float* gram_part;      // [nchunk][128][128] per-block partial Gram matrices
     int32_t* count_part;   // [nchunk][128] per-block activation counts
     double* gram;          // [128][128] reduced Gram matrix
+    float* stage;          // similarities, then counts, for the copy to the host; or null
     int nchunk;            // blocks of the partial kernel (= number of partials)
 };
 int launch_similarity(const SimArgs& a, void* stream);
 int64_t similarity_tokens_per_chunk(int E);
 int similarity_max_experts();
+int64_t similarity_stage_counts(int E);   // floats before the counts in SimArgs::stage
 
 // transition statistics and look-ahead tables on the device (lookahead.hip)
 struct LookaheadDeviceArgs {

@@ -27,6 +27,10 @@
 #include "logits_f64.hpp"
 
 namespace ordermoe {
+
+// floats before the counts in the staged outputs (8-byte aligned)
+__host__ __device__ inline int64_t sim_stage_counts(int E) { return ((int64_t)E * E + 1) & ~int64_t(1); }
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -621,7 +625,9 @@ __global__ void __launch_bounds__(RED_SLICES * RED_COLS) sim_reduce_kernel(const
 }
 
 // cosine of eq 4 from the reduced Gram matrix; a zero norm gives 0 off the
-// diagonal, every diagonal entry is 1
+// diagonal, every diagonal entry is 1.  A second copy of the similarities and
+// the counts goes side by side to a.stage (if any), for one transfer to the
+// host.
 __global__ void __launch_bounds__(256) sim_normalise_kernel(const SimArgs a, const double* gram) {
     const int p = blockIdx.x * 256 + threadIdx.x;
     const int E = a.E;
@@ -633,12 +639,16 @@ __global__ void __launch_bounds__(256) sim_normalise_kernel(const SimArgs a, con
         out = den > 0.0 ? (float)(gram[i * SIM_EMAX + j] / den) : 0.0f;
     }
     a.sim[p] = out;
+    if (!a.stage) return;
+    a.stage[p] = out;
+    if (p < E) ((int64_t*)(a.stage + sim_stage_counts(E)))[p] = a.counts[p];
 }
 
 }  // namespace
 
 int64_t similarity_tokens_per_chunk(int) { return SIM_TC; }
 int similarity_max_experts() { return SIM_EMAX; }
+int64_t similarity_stage_counts(int E) { return sim_stage_counts(E); }
 
 int launch_similarity(const SimArgs& a, void* stream) {
     hipStream_t st = (hipStream_t)stream;

@@ -105,7 +105,7 @@ def test_f32_forward_at_the_tile_edges(rows, d, f, n_shared):
     assert ro.cpu().tolist()[:n] == list(np.concatenate([[0], np.cumsum(rows)[:-1]]))
 
 
-@pytest.mark.parametrize("E,T", [(1, 1), (8, 2048), (16, 129), (17, 1000), (33, 15), (64, 700), (65, 257), (128, 1041)])
+@pytest.mark.parametrize("E,T", [(1, 1), (8, 2048), (16, 129), (17, 1000), (33, 15), (64, 700), (65, 257), (128, 1041), (128, 128), (127, 129)])
 def test_f32_similarity_at_the_partial_edges(E, T):
     """The fp32 similarity build at the edges of its partial sizes (16, 32, 64,
     128 experts) and chunks of 16 tokens.  A Gram entry sums at most 128 fp32
