@@ -6,10 +6,10 @@
 //                        the shared pseudo-expert), duplicates of one token
 //                        merged
 //   rows_scatter_kernel  each block totals the count table itself (group
-//                        offsets, its position in each group, tile counts of
-//                        the two GEMMs), then places its rows stably (token
-//                        order inside a group) with the merged gate weight
-//                        and the token -> rows map
+//                        offsets, its position in each group), then places its
+//                        rows stably (token order inside a group) with the
+//                        merged gate weight and the token -> rows map; one more
+//                        block makes the work lists of the two GEMMs
 //   rows_small_kernel    both row kernels as one block (batches of at most
 //                        1024 tokens)
 //   ggemm_bf16<.., 0>    gate/up projection, X rows gathered through row_tok,
@@ -17,18 +17,18 @@
 //   ggemm_bf16<.., 1>    down projection of the activations, epilogue scales
 //                        each row by its gate weight -> bf16 row outputs
 //   combine_kernel       y[t] = sum of t's row outputs in slot order (fp32)
-// The GEMMs are persistent: each workgroup walks the tile list, whose length
-// is read from device memory, so no host synchronisation is needed.  Tiles of
-// one expert are ordered m-fastest so consecutive tiles share a weight tile,
-// and workgroup ids are remapped so that each XCD (and its L2) works on a
-// contiguous range of tiles.  The bf16 GEMMs run whole rounds of tiles (one
-// tile per workgroup per round); the tiles left over, fewer than the grid, are
-// cut along K into pieces at the same positions in every tile when that keeps
-// at least two workgroups per tile busy, and the last workgroup to finish a
-// piece of a split tile adds the pieces in a fixed order and runs the
-// epilogue.  A shared group with a K at least twice the routed K has its tiles
-// cut into two K halves the same way, so that they no longer set the length of
-// the launch.
+// The GEMMs are persistent: each workgroup walks a tile list made on the device
+// (row counts are never read by the host).  Tiles of one expert are ordered
+// m-fastest so consecutive tiles share a weight tile, and workgroup ids are
+// remapped so that each XCD (and its L2) works on a contiguous range of tiles.
+// The bf16 GEMMs of more than 128 tokens fit the tile heights to the row counts
+// (64 to 256 rows, see TilePlan): whole rounds of tiles, one tile per workgroup
+// per round, then the tiles left over, cut along K into pieces at the same
+// positions in every tile where that ends the launch sooner; the last workgroup
+// to finish a piece of a split tile adds the pieces in a fixed order and runs
+// the epilogue.  A shared group with a K at least twice the routed K has its
+// tiles cut into up to four K pieces the same way, so that they do not set the
+// length of the launch.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -46,14 +46,55 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int FT_TB = 256;        // tokens per block in the row kernels
 constexpr int MAXG = ORDERMOE_MAX_LOCAL + 1;
 constexpr int MAXR = ORDERMOE_MAX_TOPK + 1;   // rows per token (routed + shared)
-// bf16 GEMM launches: at most SK_MAX_GRID workgroups.  Split tiles use one
-// partial tile per workgroup (its slot) and one arrival counter per split
-// tile, in one array of SK_MAX_GRID counters per GEMM (gate/up, down), zeroed
-// by the row kernels before every forward.  A tile is cut into at most
-// SK_SPLIT pieces (the last arrival reads them all).
+// bf16 GEMM launches: at most SK_MAX_GRID workgroups.  Every piece of a split
+// tile has a slot for its partial tile, every split tile an arrival counter in
+// one array of SK_MAX_GRID counters per GEMM (gate/up, down), zeroed by the row
+// kernels before every forward.  A tile is cut into at most SK_SPLIT pieces (the
+// last arrival reads them all).
 constexpr int SK_MAX_GRID = 256;
 constexpr int SK_SPLIT = 4;
-constexpr int SK_MIN_PIECE_KT = 16;   // K tiles of 64 per piece, at least
+constexpr int SK_MIN_PIECE_KT = 8;    // K tiles of 64 per piece, at least
+// partial tiles of H x 64 rows in the workspace of SK_MAX_GRID whole tiles, whose
+// last one's place holds the work lists
+__host__ __device__ constexpr int sk_slots(int H) { return 4 * (SK_MAX_GRID - 1) / H; }
+
+// Work list of a bf16 tiled GEMM, written by the row kernels for the launch that
+// follows.  A group of R rows is covered by tiles of 64 H rows, H = 1 .. 4 chosen
+// for the launch, and one last tile of as many 64-row units as the remainder
+// needs.  The shared group comes first, then the routed groups; inside a group
+// tiles are m-fastest, so that the tiles that read one weight tile run together.
+constexpr int TP_BN = 256;
+struct __attribute__((aligned(16))) TileSeg {
+    int32_t first;            // the group's first work item
+    int32_t mt_hl;            // row tiles * 8 + height of the last one in units of 64 rows
+    int32_t off, R;           // first row, rows
+};
+struct __attribute__((aligned(16))) TilePlan {
+    int32_t H;                // tile height in units of 64 rows
+    int32_t rounds, items;    // whole rounds of the grid, work items (a shared tile counts once per K piece)
+    int32_t sp0, split;       // items from sp0 on are cut along K into `split` pieces
+    int32_t spread;           // the last, partial round is shared evenly by the XCDs
+    int32_t q, nsh;           // K pieces of a shared tile, shared tiles
+    TileSeg seg[ORDERMOE_MAX_LOCAL + 1];   // [g]; n_local: the shared group
+};
+// what the work list of one GEMM is made from: column tiles and K tiles of the
+// routed and shared groups, K pieces of a shared tile wished for, workgroups
+struct PlanShape {
+    int32_t nt_r, nt_s, kt_r, kt_s, q, grid;
+    uint32_t grid_inv;        // 2^32 / grid, rounded up
+};
+// Time of a tile of h 64-row units over kt K tiles of 64, in hundredths of the
+// time of one K tile of a 256-row tile (1.5 us in a full chip): the K loop by
+// height, and about five K tiles' time of start and epilogue.  The constants,
+// and split_time below, were fitted to both GEMMs of the Mixtral-, Qwen-,
+// DeepSeek- and 128-expert-shaped layers at 1000 to 16000 tokens, each timed
+// with every height: the height that plan_tiles picks is on average 0.9% slower
+// than the fastest of the four.
+__host__ __device__ constexpr int tile_time(int h, int kt) {
+    return kt * (h == 1 ? 50 : h == 2 ? 56 : h == 3 ? 74 : 100) + 500;
+}
+// storing and adding up the `pieces` partial tiles of a tile of height h
+__host__ __device__ constexpr int split_time(int h, int pieces) { return h * (100 + 150 * pieces); }
 
 struct RowsArgs {
     int64_t T;
@@ -74,6 +115,9 @@ struct RowsArgs {
     // tile geometry for the tile counts
     int bm_gu, bn_gu, bm_dn, bn_dn;
     int n_gu_r, n_gu_s, n_dn;
+    // bf16 tiled GEMMs: work lists of gate/up and down, published by the row kernels (null otherwise)
+    TilePlan* plan;           // [2]
+    PlanShape shape[2];
 };
 
 // One token's slots as read from memory: executing server, expert and gate
@@ -161,6 +205,41 @@ __device__ inline void wave_group_ranks(unsigned long long* msk, int G, int lane
     for (int g = lane; g < G; g += 64) wcnt[g] = __popcll(msk[g]);
 }
 
+// Inclusive scans over the 64 lanes of a wave by DPP row shifts and row
+// broadcasts (a dozen cycles a step; a step through ds_bpermute waits for LDS,
+// and the scans of the row kernels are a serial chain of them).  Lane 63 holds
+// the total.  All lanes take part.
+template <int CTRL, int ROWS>
+__device__ inline int dpp_or0(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
+__device__ inline int wave_scan_add(int v) {
+    v += dpp_or0<0x111, 0xF>(v);   // row_shr:1
+    v += dpp_or0<0x112, 0xF>(v);
+    v += dpp_or0<0x114, 0xF>(v);
+    v += dpp_or0<0x118, 0xF>(v);
+    v += dpp_or0<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp_or0<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ inline int wave_max_nonneg(int v) {     // of values >= 0
+    int o;
+    o = dpp_or0<0x111, 0xF>(v); v = o > v ? o : v;
+    o = dpp_or0<0x112, 0xF>(v); v = o > v ? o : v;
+    o = dpp_or0<0x114, 0xF>(v); v = o > v ? o : v;
+    o = dpp_or0<0x118, 0xF>(v); v = o > v ? o : v;
+    o = dpp_or0<0x142, 0xA>(v); v = o > v ? o : v;
+    o = dpp_or0<0x143, 0xC>(v); v = o > v ? o : v;
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ inline float wave_sum_f(float v) {
+    v += __int_as_float(dpp_or0<0x111, 0xF>(__float_as_int(v)));
+    v += __int_as_float(dpp_or0<0x112, 0xF>(__float_as_int(v)));
+    v += __int_as_float(dpp_or0<0x114, 0xF>(__float_as_int(v)));
+    v += __int_as_float(dpp_or0<0x118, 0xF>(__float_as_int(v)));
+    v += __int_as_float(dpp_or0<0x142, 0xA>(__float_as_int(v)));
+    v += __int_as_float(dpp_or0<0x143, 0xC>(__float_as_int(v)));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 __global__ void __launch_bounds__(FT_TB) rows_count_kernel(const RowsArgs a) {
     __shared__ int32_t s_lidx[ORDERMOE_MAX_EXPERTS];
     __shared__ int32_t s_h[MAXG];
@@ -191,44 +270,162 @@ constexpr int SCAN_WAVES = SCAN_THREADS / 64;
 // row offsets and the tile counts of the two GEMMs into device memory.
 __device__ inline void group_layout(const RowsArgs& a, const int32_t* tot, int32_t* first, int lane, bool publish) {
     const int G = a.n_local + a.has_shared;
-    int32_t base = 0;
-    int64_t tiles_gu = 0, tiles_dn = 0;
+    int32_t base = 0, tiles_gu = 0, tiles_dn = 0;
     for (int g0 = 0; g0 <= a.n_local; g0 += 64) {
         const int g = g0 + lane;
         const int32_t R = g < G ? tot[g] : 0;
-        int32_t inc = R;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int32_t o = __shfl_up(inc, off);
-            if (lane >= off) inc += o;
-        }
+        const int32_t inc = wave_scan_add(R);
         if (g <= a.n_local) {
             first[g] = base + inc - R;
             if (publish) a.row_offsets[g] = base + inc - R;
         }
-        int64_t tg = 0, td = 0;
-        if (g < G) {
-            const bool sh = g == a.n_local;
-            tg = (int64_t)((R + a.bm_gu - 1) / a.bm_gu) * ((sh ? a.n_gu_s : a.n_gu_r) / a.bn_gu);
-            td = (int64_t)((R + a.bm_dn - 1) / a.bm_dn) * (a.n_dn / a.bn_dn);
+        base += __builtin_amdgcn_readlane(inc, 63);
+        // the tile counts of the untiled GEMM paths
+        if (publish && !a.plan) {
+            int32_t tg = 0, td = 0;
+            if (g < G) {
+                const bool sh = g == a.n_local;
+                tg = (R + a.bm_gu - 1) / a.bm_gu * ((sh ? a.n_gu_s : a.n_gu_r) / a.bn_gu);
+                td = (R + a.bm_dn - 1) / a.bm_dn * (a.n_dn / a.bn_dn);
+            }
+            tiles_gu += __builtin_amdgcn_readlane(wave_scan_add(tg), 63);
+            tiles_dn += __builtin_amdgcn_readlane(wave_scan_add(td), 63);
         }
-        for (int off = 32; off >= 1; off >>= 1) {
-            tg += __shfl_xor(tg, off);
-            td += __shfl_xor(td, off);
-        }
-        tiles_gu += tg;
-        tiles_dn += td;
-        base += __shfl(inc, 63);
     }
     if (publish && lane == 0) {
         a.row_offsets[a.n_local + 1] = base;
-        a.tile_info[0] = (int32_t)tiles_gu;
-        a.tile_info[1] = (int32_t)tiles_dn;
+        a.tile_info[0] = tiles_gu;
+        a.tile_info[1] = tiles_dn;
         a.tile_info[2] = base;
         a.tile_info[3] = 0;
     }
 }
 
-// Placement of every row, one block per block of rows_count_kernel.  Each
+// x / n for x < 2^16 + 4 and n = 1 .. 4
+__device__ inline int div4(int x, int n) { return n == 3 ? (int)(((uint32_t)x * 43691u) >> 17) : x >> (n >> 1); }
+
+// The work list of one GEMM with tiles of 64 H rows and the estimated time of the
+// launch, by one wave: lane g holds routed group g (R rows; Rs: shared rows).
+struct PlanTry {
+    float time;
+    int first, mt_hl, mts_hls;                     // lane g; shared
+    int rounds, items, sp0, split, spread, q, nsh;
+};
+__device__ inline PlanTry plan_tiles(const PlanShape& c, int R, int Rs, int lane, int H) {
+    PlanTry o;
+    const int u = (R + 63) >> 6, us = (Rs + 63) >> 6;            // (bf16: fewer than 2^22 rows)
+    const int mt = div4(u + H - 1, H), hl = u - (mt - 1) * H;    // (mt = 0: unused)
+    const int mts = div4(us + H - 1, H), hls = us - (mts - 1) * H;
+    o.mt_hl = mt * 8 + (mt ? hl : 0);
+    o.mts_hls = mts * 8 + (mts ? hls : 0);
+    const int nsh = mts * c.nt_s, hs = mts > 1 ? H : hls;
+    // the routed items: their number, their total time, the tallest one
+    int inc = mt * c.nt_r, hmax = mt > 1 ? H : mt == 1 ? hl : 0;
+    const int t_h = tile_time(H, c.kt_r);
+    float sum_r = mt > 0 ? (float)c.nt_r * ((float)(mt - 1) * (float)t_h + (float)tile_time(hl, c.kt_r)) : 0.f;
+    inc = wave_scan_add(inc);
+    hmax = wave_max_nonneg(hmax);
+    sum_r = wave_sum_f(sum_r);
+    const int items_r = __builtin_amdgcn_readlane(inc, 63);
+    const int long_r = hmax ? tile_time(hmax, c.kt_r) : 0, h_last = hmax ? hmax : hs;
+    // shared tiles with a K of at least twice the routed K may be cut into up to
+    // c.q pieces along K, as far as the slots and counters go
+    const int qmax = nsh > 0 && nsh <= SK_MAX_GRID ? c.q : 1;
+    o.time = 3.0e38f;
+    for (int q = 1; q <= qmax && (q == 1 || q * nsh <= sk_slots(H)); ++q) {
+        const int kt_q = div4(c.kt_s, q);
+        const int sh_items = nsh * q, items = sh_items + items_r;
+        float sum = sum_r;
+        int longest = long_r;
+        if (nsh > 0) {
+            const int fix = q > 1 ? split_time(hs, q) : 0, ts = tile_time(hs, kt_q) + fix;
+            longest = ts > longest ? ts : longest;
+            sum += (float)(c.nt_s * q) *
+                   ((float)(mts - 1) * (float)tile_time(H, kt_q) + (float)tile_time(hls, kt_q) + (float)(mts * fix));
+        }
+        // whole rounds, then the items left over; the routed ones of these are cut
+        // along K into `split` pieces when that ends the launch sooner
+        // (fewer than 2^20 items, so the multiplication is exact)
+        const int rounds = (int)__umulhi((uint32_t)items, c.grid_inv), head = rounds * c.grid, left = items - head;
+        const int sp0 = q > 1 && sh_items > head ? sh_items : head, ns = items - sp0, whole = sp0 - head;
+        const float mean = items > 0 ? sum * __builtin_amdgcn_rcpf((float)items) : 0.f;
+        const bool routed = head >= sh_items && hmax;            // the items left over are routed ones
+        const float tail = (float)(routed ? long_r : longest);
+        float base = 0.f;
+        if (rounds > 0) {
+            base = (float)rounds * mean + (tail > mean ? 0.5f * (tail - mean) : 0.f);
+            if (base < (float)longest) base = (float)longest;
+        }
+        float best = base + (left > 0 ? tail : 0.f);
+        // after one round, the snake order gives the items left over to the workgroups
+        // that ran routed tiles while the others are still at their long shared ones
+        if (rounds == 1 && routed && left > 0 && left <= head - sh_items && longest > long_r) {
+            best = base - (float)(longest - long_r) + tail;
+            if (best < (float)longest) best = (float)longest;
+        }
+        int split = 1;
+        const bool even = nsh == 0 || 2 * kt_q <= 3 * c.kt_r;    // else a long shared tile outlasts the pieces
+#pragma unroll
+        for (int s = 2; s <= SK_SPLIT; ++s) {
+            const int kp = div4(c.kt_r, s);
+            const bool can = ns > 0 && even && whole + s * ns <= c.grid && (q > 1 ? sh_items : 0) + s * ns <= sk_slots(H) &&
+                             ns + (q > 1 ? nsh : 0) <= SK_MAX_GRID && kp >= SK_MIN_PIECE_KT;
+            int t = tile_time(h_last, kp) + split_time(h_last, s);
+            if (whole > 0 && t < longest) t = longest;
+            if (can && base + (float)t < best) { best = base + (float)t; split = s; }
+        }
+        if (best < o.time) {
+            o.time = best;
+            o.first = sh_items + inc - mt * c.nt_r;
+            o.rounds = rounds; o.items = items; o.sp0 = sp0; o.split = split; o.q = q; o.nsh = nsh;
+            // the last, partial round is spread over the XCDs when every tile has about
+            // the same K; otherwise the snake order gives it to the workgroups that just
+            // ran short tiles
+            o.spread = even;
+        }
+    }
+    return o;
+}
+
+// The work lists of both GEMMs: each of PW waves (4 or 8) tries tiles of one
+// height, for one GEMM (8) or both (4), and the wave with the least estimate of a
+// GEMM publishes.  publish_try, a barrier of the block, publish_best.
+template <int PW>
+__device__ inline void publish_try(const RowsArgs& a, const int32_t* tot, int lane, int wave, float (*s_est)[4], PlanTry* o) {
+    const int n = a.n_local;
+    const int R = lane < n ? tot[lane] : 0, Rs = a.has_shared ? tot[n] : 0;
+#pragma unroll
+    for (int i = 0; i < 8 / PW; ++i) {
+        const int w = PW == 8 ? wave >> 2 : i;
+        o[i] = plan_tiles(a.shape[w], R, Rs, lane, 4 - (wave & 3));
+        if (lane == 0) s_est[w][wave & 3] = o[i].time;
+    }
+}
+template <int PW>
+__device__ inline void publish_best(const RowsArgs& a, const int32_t* tot, const int32_t* first, int lane, int wave,
+                                    const float (*s_est)[4], const PlanTry* o) {
+    const int n = a.n_local;
+#pragma unroll
+    for (int i = 0; i < 8 / PW; ++i) {
+        const int w = PW == 8 ? wave >> 2 : i;
+        int bw = 0;
+        float best = s_est[w][0];
+#pragma unroll
+        for (int j = 1; j < 4; ++j)
+            if (s_est[w][j] < best) { best = s_est[w][j]; bw = j; }
+        if (bw != (wave & 3)) continue;
+        TilePlan* P = a.plan + w;
+        if (lane == 0) {
+            P->H = 4 - bw; P->rounds = o[i].rounds; P->items = o[i].items; P->sp0 = o[i].sp0; P->split = o[i].split;
+            P->spread = o[i].spread; P->q = o[i].q; P->nsh = o[i].nsh;
+            P->seg[n] = TileSeg{0, o[i].mts_hls, a.has_shared ? first[n] : 0, a.has_shared ? tot[n] : 0};
+        }
+        if (lane < n) P->seg[lane] = TileSeg{o[i].first, o[i].mt_hl, first[lane], tot[lane]};
+    }
+}
+
+// Placement of every row, one block per block of rows_count_kernel, and for the
+// bf16 GEMMs one block more that makes their work lists meanwhile.  Each
 // block first totals the count table on its own (groups x blocks integers):
 // its first row inside each group (the counts of the blocks before it) and the
 // group totals, whose exclusive scan gives the group offsets; block 0 also
@@ -241,7 +438,8 @@ __global__ void __launch_bounds__(FT_TB) rows_scatter_kernel(const RowsArgs a) {
     __shared__ unsigned long long s_msk[FT_TB / 64][MAXG];
     __shared__ int32_t s_lo[MAXG], s_tot[MAXG];
     __shared__ int32_t s_first[MAXG];        // first row of this block in each group
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_est[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = a.n_local + a.has_shared;
     const int b = (int)blockIdx.x;
     const int64_t t = (int64_t)b * FT_TB + tid;
@@ -264,6 +462,16 @@ __global__ void __launch_bounds__(FT_TB) rows_scatter_kernel(const RowsArgs a) {
         if (lane == 0) { s_lo[g] = lo; s_tot[g] = tot; }
     }
     __syncthreads();
+    if (b == a.nblk) {
+        // the block past the rows: work lists of the GEMMs (t >= T: no rows here)
+        if (wave == 0) group_layout(a, s_tot, s_first, lane, false);
+        static_assert(FT_TB / 64 == 4, "one wave per tile height");
+        PlanTry o[2];
+        publish_try<4>(a, s_tot, lane, wave, s_est, o);
+        __syncthreads();
+        publish_best<4>(a, s_tot, s_first, lane, wave, s_est, o);
+        return;
+    }
     int grp[MAXR], rank[MAXR];
     float ws[MAXR];
     int n = 0;
@@ -305,7 +513,8 @@ __global__ void __launch_bounds__(SCAN_THREADS) rows_small_kernel(const RowsArgs
     __shared__ int32_t s_wcnt[SCAN_WAVES][MAXG];
     __shared__ unsigned long long s_msk[SCAN_WAVES][MAXG];
     __shared__ int32_t s_first[MAXG], s_tot[MAXG];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_est[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = a.n_local + a.has_shared;
     const int64_t t = tid;
     TokSlots ts;
@@ -324,15 +533,21 @@ __global__ void __launch_bounds__(SCAN_THREADS) rows_small_kernel(const RowsArgs
     }
     wave_group_ranks(s_msk[wave], G, lane, grp, n, rank, s_wcnt[wave]);
     __syncthreads();
-    if (wave == 0) {
-        for (int g = lane; g < G; g += 64) {
-            int32_t R = 0;
-            for (int w = 0; w < SCAN_WAVES; ++w) R += s_wcnt[w][g];
-            s_tot[g] = R;
-        }
-        group_layout(a, s_tot, s_first, lane, true);
+    if (tid < G) {
+        int32_t R = 0;
+        for (int w = 0; w < SCAN_WAVES; ++w) R += s_wcnt[w][tid];
+        s_tot[tid] = R;
     }
     __syncthreads();
+    // the last eight waves, which hold the fewest tokens, make the GEMMs' work lists
+    // while wave 0 lays out the groups
+    constexpr int PW0 = SCAN_WAVES - 8;
+    const bool planner = a.plan && wave >= PW0;
+    PlanTry o[1];
+    if (wave == 0) group_layout(a, s_tot, s_first, lane, true);
+    if (planner) publish_try<8>(a, s_tot, lane, wave - PW0, s_est, o);
+    __syncthreads();
+    if (planner) publish_best<8>(a, s_tot, s_first, lane, wave - PW0, s_est, o);
     if (t < a.T) {
         const int stride = a.k + 1;
 #pragma unroll
@@ -418,7 +633,9 @@ struct GemmArgs {
     void* Or;                 // mode 0: routed activations out; mode 1: row outputs [*][Nr]
     void* Os;                 // mode 0: shared activations out; mode 1: unused
     const float* row_w;       // mode 1
-    float* sk_part;           // bf16: [SK_MAX_GRID][BM * BN] partial tiles of split tiles
+    const TilePlan* plan;     // bf16 tiled: the work list
+    int stream;               // bf16 tiled gate/up: see STREAM_BYTES
+    float* sk_part;           // bf16 tiled: [sk_slots(H)][64 H * 256] partial tiles of split tiles
     int32_t* sk_cnt;          // bf16: [2][SK_MAX_GRID] arrival counters (zero at launch)
 };
 
@@ -548,23 +765,27 @@ __device__ inline void sched_interleave() {
     }
 }
 
-// bf16 grouped GEMM C = A B^T per tile of BM x BN, K step 64, 4 waves (2 x 2),
-// each wave a (BM/2) x (BN/2) block of v_mfma_f32_32x32x16_bf16 tiles.
-// Operands go from memory straight into LDS (buffer loads to LDS), two
-// buffers; the layout is described at the K loop.  The K position travels in
-// the buffer load's scalar offset, and rows past the end of a group read as
-// zeros through the buffer range check (their offset is set past the buffer).
-// Byte offsets inside one operand fit in 31 bits (checked by the host).
-//
-// Work: rounds of whole tiles while a round fills the grid; the tiles left
-// over are cut along K into equal pieces when that puts at least two
-// workgroups on each (split-K), else they run whole as a last, partial round.
-// A piece stores its fp32 partial tile in its slot, and the workgroup whose
-// arrival completes the tile's counter sums the tile's pieces in K order (so
-// the result does not depend on who is last) and runs the epilogue.  No
-// workgroup waits for another.
-template <int BM, int BN, int MODE>
-__global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
+// bf16 grouped GEMM C = A B^T per tile of BM x 256, K step 64, 4 waves (2 x 2),
+// each wave a (BM/2) x 128 block of v_mfma_f32_32x32x16_bf16 tiles.  Operands go
+// from memory straight into LDS (buffer loads to LDS), two buffers of A and
+// three of B, [rows][64] bf16 each; the layout is described at the K loop.  The
+// K position travels in the buffer load's scalar offset, and rows past the end
+// of a group read as zeros through the buffer range check (their offset is set
+// past the buffer).  Byte offsets inside one operand fit in 31 bits (checked by
+// the host).  A piece of a split tile stores its fp32 partial tile in its slot,
+// and the workgroup whose arrival completes the tile's counter sums the tile's
+// pieces in K order (so the result does not depend on who is last) and runs the
+// epilogue.  No workgroup waits for another.
+// One tile (or K piece of a tile): BM x 256 outputs over the K tiles
+// [kt_lo, kt_hi).  nseg > 1: piece of a split tile, its partial sums in slot
+// pslot, the tile's pieces in slots pslot0 + i * sstride, arrivals counted in
+// counter ctr.
+template <int BM, int MODE, int BAUX = 0>
+__device__ __attribute__((always_inline)) inline void bf16_tile(const GemmArgs& p, const TileLoc& L, int kt_lo, int kt_hi,
+                                                                int nseg, int ctr, int pslot, int pslot0, int sstride,
+                                                                uint32_t slot_bytes, __bf16* sA0, __bf16* sA1, __bf16* sB0, __bf16* sB1,
+                                                                __bf16* sB2) {
+    constexpr int BN = TP_BN;
     constexpr int BK = 64;
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int FM = WM / 32, FN = WN / 32;
@@ -572,430 +793,423 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
     constexpr int BV = BN / 32;
     static_assert(FN % 2 == 0, "gate/up pairs need an even number of 32-column blocks");
     static_assert(BM % 64 == 0 && BN % 64 == 0, "an even number of load instructions per wave");
-    // two buffers of the A and B tiles, [rows][64] bf16 each
-    // two buffers of the A tile and three of the B tile, [rows][64] bf16 each
-    __shared__ __attribute__((aligned(16))) __bf16 sA0[BM * 64], sA1[BM * 64], sB0[BN * 64], sB1[BN * 64];
-    __shared__ __attribute__((aligned(16))) __bf16 sB2[BN * 64];
-    // the split-tile arrival flag lives in sB2, which is idle from the end of a
-    // K loop until the first K tile of the next one (a prologue loads sA0, sA1,
-    // sB0 and sB1 only), so that the buffers of 256 x 256 tiles fill the LDS
-    int* const s_last = (int*)sB2;
-    // down: the gate weights of the tile's rows, for the epilogue; 256-row tiles
-    // keep them in sB2 too (past the flag), so that their buffers fill the LDS
-    constexpr bool ROWW_IN_SB2 = MODE == 1 && (2 * BM + 3 * BN) * 64 * 2 + BM * 4 > 160 * 1024;
-    static_assert(!ROWW_IN_SB2 || 256 + BM * 4 <= BN * 64 * 2, "flag and row weights fit sB2");
-    float* s_roww;
-    if constexpr (ROWW_IN_SB2) {
-        s_roww = (float*)sB2 + 64;
-    } else {
-        __shared__ float s_roww_own[MODE == 1 ? BM : 1];
-        s_roww = s_roww_own;
-    }
-
-    const int tid = threadIdx.x;
-    const int total = *p.ntiles;
-    const int grid = (int)gridDim.x;                // a multiple of 8, at most SK_MAX_GRID
-    const int vid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
     constexpr uint32_t OOR = 0x80000000u;           // offset past every buffer: reads zero
-    // A shared group whose K is at least twice the routed K (the down
-    // projection of several shared experts) has tiles that outlast the routed
-    // ones several times over.  When the grid holds two pieces of each, every
-    // shared tile is cut along K into two halves: work item i < 2 nsh is half
-    // i / nsh of shared tile i mod nsh (the shared tiles come first in the
-    // list), and the routed tiles follow as whole items, so that they fill in
-    // around the halves.
-    int nsh = 0;
-    if (p.G > p.n_routed) {
-        const int rsh = p.offsets[p.n_routed + 1] - p.offsets[p.n_routed];
-        nsh = (rsh + BM - 1) / BM * (p.Ns / BN);
+    // the split-tile arrival flag and (down) the gate weights of the tile's rows
+    // live in sB2, which is idle from the end of a K loop until the first K tile
+    // of the next one (a prologue loads sA0, sA1, sB0 and sB1 only), so that the
+    // buffers of 256-row tiles fill the LDS
+    int* const s_last = (int*)sB2;
+    float* const s_roww = (float*)sB2 + 64;
+    static_assert(256 + BM * 4 <= BN * 64 * 2, "flag and row weights fit sB2");
+    // the thread index passes through an empty asm once per tile, so that
+    // the thread-dependent offsets below are recomputed per tile instead of
+    // being held (and spilled to scratch) across the whole persistent loop
+    int tid_r = threadIdx.x;
+    asm volatile("" : "+v"(tid_r));
+    const int lane_r = tid_r & 63, wave_r = tid_r >> 6;
+    const int wm_r = wave_r >> 1, wn_r = wave_r & 1;
+    // the wave index as a scalar: the LDS destinations of the loads into LDS
+    // (the M0 operand) are then scalar expressions, not VGPRs held per buffer
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave_r);
+    const bool shared = L.g >= p.n_routed;
+    const int K = L.K;
+    const __bf16* Bw = shared ? (const __bf16*)p.Ws
+                              : (const __bf16*)p.Wr + (size_t)L.g * L.N * K;
+    const __amdgpu_buffer_rsrc_t rb_rs = make_rsrc(Bw, (uint32_t)((size_t)L.N * K * 2));
+    // LDS rows of 64 K values (128 bytes, unpadded); 16-byte chunk q of
+    // row r holds the operand's chunk q ^ ((r >> 1) & 7), so that the 16
+    // rows a fragment read serves per LDS cycle (16 lanes of 16 bytes over
+    // the 64 banks) fall on distinct banks.  Load instruction v of wave_r w
+    // covers rows (w AV + v) 8 .. +7 of the tile: lane_r l takes row + l / 8
+    // and fetches the chunk that the direct-to-LDS load writes at position
+    // l & 7 of that row, (l & 7) ^ ((r >> 1) & 7); with AV, BV even that is
+    // gc0 for even v and gc1 for odd v.
+    const int gc0 = (lane_r & 7) ^ (lane_r >> 4);
+    const int gc1 = (lane_r & 7) ^ (4 | (lane_r >> 4));
+    const int rsub = lane_r >> 3;
+    // A: the gathered token rows of X (gate/up) or the group's activation rows (down)
+    const __bf16* Ab = MODE == 0 ? (const __bf16*)p.X
+                                 : (shared ? (const __bf16*)p.As : (const __bf16*)p.Ar + (size_t)L.rowbase * K);
+    const __amdgpu_buffer_rsrc_t ra_rs =
+        make_rsrc(Ab, MODE == 0 ? p.x_bytes : (uint32_t)((size_t)L.R * K * 2));
+    // down: thread tid_r < BM reads the gate weight of tile row tid_r now (one
+    // branch-free load, rows past the group read zero) and parks it in LDS
+    // after the K loop, so that the epilogue waits for no global load
+    float roww = 0.f;
+    if constexpr (MODE == 1) {
+        const __amdgpu_buffer_rsrc_t rw_rs = make_rsrc(p.row_w + L.rowbase, (uint32_t)L.R * 4u);
+        const int rr = L.m0 + tid_r;
+        roww = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                             rw_rs, tid_r < BM && rr < L.R ? rr * 4 : (int)OOR, 0, 0));
     }
-    const bool sh_split = nsh > 0 && p.Ks >= 2 * p.Kr && p.Ks % (4 * BK) == 0 && 2 * nsh <= grid;
-    const int items = sh_split ? total + nsh : total;
-    const int rounds = items / grid, head = rounds * grid;
+    uint32_t aoff[AV];
+#pragma unroll
+    for (int v = 0; v < AV; ++v) {
+        const int row = L.m0 + (wave_r * AV + v) * 8 + rsub;
+        const uint32_t src = MODE == 0 ? (row < L.R ? (uint32_t)p.row_tok[L.rowbase + row] : 0u) : (uint32_t)row;
+        aoff[v] = row < L.R ? (src * (uint32_t)(MODE == 0 ? p.ldx : K) + ((v & 1) ? gc1 : gc0) * 8) * 2u : OOR;
+    }
+    // B: the blocked weights (256-row blocks of 64-deep K steps, 128-byte
+    // rows): load instruction v of wave_r w covers rows (w BV + v) 8 .. +7
+    // of the tile's block, 1 KB in a row; the K step goes in the scalar offset
+    static_assert(BN == WB_ROWS, "a tile's weight rows are one block");
+    const uint32_t bblk = (uint32_t)(L.n0 / BN) * (uint32_t)(K / WB_K) * (uint32_t)(BN * WB_K * 2) +
+                          (uint32_t)(wave_r * BV * 8 + rsub) * (WB_K * 2u);
 
-    // the tiles left after the whole rounds: when at least two workgroups per
-    // tile are free, each tile is cut along K into `split` pieces at the same
-    // positions in every tile (piece j of the tile at head + i goes to
-    // position j * left + i of the round), so that the workgroups of an XCD
-    // read the same K range of neighbouring tiles together, as in a whole
-    // round.  Positions follow the snake order of the rounds.  Only when all
-    // tiles have the same K: then every workgroup finishes its rounds at about
-    // the same time (a shared group with a longer K keeps some workgroups busy
-    // while the pieces would go out).
-    const int left = items - head;
-    int split = left > 0 ? grid / left : 0;
-    if (split > SK_SPLIT) split = SK_SPLIT;
-    if (split > p.Kr / (2 * BK)) split = p.Kr / (2 * BK);
-    // a piece keeps at least SK_MIN_PIECE_KT K tiles: shorter pieces cost more
-    // in partial-tile stores and fix-up reads than the idle workgroups they
-    // fill, most of all when another batch's kernels can take those CUs
-    if (split > p.Kr / BK / SK_MIN_PIECE_KT) split = p.Kr / BK / SK_MIN_PIECE_KT;
-    if (p.G > p.n_routed && p.Ks != p.Kr) split = 1;
-    // slots of the pieces of one split tile lie sstride apart
-    const int sstride = sh_split ? nsh : left;
-    // the last, partial round is spread over the XCDs when every tile has the
-    // same K; otherwise the snake order gives it to the workgroups that just
-    // ran short tiles
-    const bool spread = !(p.G > p.n_routed && p.Ks != p.Kr);
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    for (int r = 0; r <= rounds; ++r) {
-        // the thread index passes through an empty asm once per tile, so that
-        // the thread-dependent offsets below are recomputed per tile instead of
-        // being held (and spilled to scratch) across the whole persistent loop
-        int tid_r = tid;
-        asm volatile("" : "+v"(tid_r));
-        const int lane_r = tid_r & 63, wave_r = tid_r >> 6;
-        const int wm_r = wave_r >> 1, wn_r = wave_r & 1;
-        // the wave index as a scalar: the LDS destinations of the loads into LDS
-        // (the M0 operand) are then scalar expressions, not VGPRs held per buffer
-        const int wave_u = __builtin_amdgcn_readfirstlane(wave_r);
-        // (scanned per tile: held across the K loop it would spill)
-        const GroupScan gs = scan_groups<BM, BN>(p, lane_r);
-        TileLoc L;
-        int kt_lo = 0, kt_hi = 0;       // K tiles of 64 of this piece
-        int nseg = 1, ctr = 0, pslot = 0;
-        if (r < rounds || split < 2) {
-            // whole tiles (or shared halves) in rounds of `grid`, in snake
-            // order (odd rounds reversed), so that the workgroups that took
-            // the long tiles at the head of the list take the last tiles of
-            // the next round; the last round may be partial
-            const int pos = round_pos(vid, r, r < rounds ? grid : items - head, grid, spread);
-            if (pos < 0) break;
-            const int item = r * grid + pos;
-            if (item >= items) break;
-            if (sh_split && item < 2 * nsh) {
-                const int j = item / nsh;
-                ctr = item - j * nsh;
-                pslot = item;
-                if (!find_tile<BM, BN>(p, gs, ctr, lane_r, L)) break;
-                const int half = L.K / (2 * BK);          // even: K is a multiple of 4 BK
-                kt_lo = j * half;
-                kt_hi = kt_lo + half;
-                nseg = 2;
-            } else {
-                if (!find_tile<BM, BN>(p, gs, sh_split ? item - nsh : item, lane_r, L)) break;
-                kt_hi = L.K / BK;
-            }
-        } else {
-            const int pos = round_pos(vid, rounds, split * left, grid, spread);
-            if (pos < 0) break;
-            const int j = pos / left;
-            ctr = pos - j * left;
-            pslot = pos;
-            if (!find_tile<BM, BN>(p, gs, head + ctr, lane_r, L)) break;
-            const int units = L.K / (2 * BK);
-            kt_lo = 2 * (j * units / split);
-            kt_hi = 2 * ((j + 1) * units / split);
-            nseg = split;
-        }
-        const bool shared = L.g >= p.n_routed;
-        const int K = L.K;
-        const __bf16* Bw = shared ? (const __bf16*)p.Ws
-                                  : (const __bf16*)p.Wr + (size_t)L.g * L.N * K;
-        const __amdgpu_buffer_rsrc_t rb_rs = make_rsrc(Bw, (uint32_t)((size_t)L.N * K * 2));
-        // LDS rows of 64 K values (128 bytes, unpadded); 16-byte chunk q of
-        // row r holds the operand's chunk q ^ ((r >> 1) & 7), so that the 16
-        // rows a fragment read serves per LDS cycle (16 lanes of 16 bytes over
-        // the 64 banks) fall on distinct banks.  Load instruction v of wave_r w
-        // covers rows (w AV + v) 8 .. +7 of the tile: lane_r l takes row + l / 8
-        // and fetches the chunk that the direct-to-LDS load writes at position
-        // l & 7 of that row, (l & 7) ^ ((r >> 1) & 7); with AV, BV even that is
-        // gc0 for even v and gc1 for odd v.
-        const int gc0 = (lane_r & 7) ^ (lane_r >> 4);
-        const int gc1 = (lane_r & 7) ^ (4 | (lane_r >> 4));
-        const int rsub = lane_r >> 3;
-        // A: the gathered token rows of X (gate/up) or the group's activation rows (down)
-        const __bf16* Ab = MODE == 0 ? (const __bf16*)p.X
-                                     : (shared ? (const __bf16*)p.As : (const __bf16*)p.Ar + (size_t)L.rowbase * K);
-        const __amdgpu_buffer_rsrc_t ra_rs =
-            make_rsrc(Ab, MODE == 0 ? p.x_bytes : (uint32_t)((size_t)L.R * K * 2));
-        // down: thread tid_r < BM reads the gate weight of tile row tid_r now (one
-        // branch-free load, rows past the group read zero) and parks it in LDS
-        // after the K loop, so that the epilogue waits for no global load
-        float roww = 0.f;
-        if constexpr (MODE == 1) {
-            const __amdgpu_buffer_rsrc_t rw_rs = make_rsrc(p.row_w + L.rowbase, (uint32_t)L.R * 4u);
-            const int rr = L.m0 + tid_r;
-            roww = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                 rw_rs, tid_r < BM && rr < L.R ? rr * 4 : (int)OOR, 0, 0));
-        }
-        uint32_t aoff[AV];
+    // the loads of a K tile go from memory straight into LDS buffer b
+    auto dmaA = [&](__bf16* sa, int k0) {
 #pragma unroll
         for (int v = 0; v < AV; ++v) {
-            const int row = L.m0 + (wave_r * AV + v) * 8 + rsub;
-            const uint32_t src = MODE == 0 ? (row < L.R ? (uint32_t)p.row_tok[L.rowbase + row] : 0u) : (uint32_t)row;
-            aoff[v] = row < L.R ? (src * (uint32_t)(MODE == 0 ? p.ldx : K) + ((v & 1) ? gc1 : gc0) * 8) * 2u : OOR;
+            // (a local copy: the host pass drops the kernel when an array
+            // element captured by reference is the builtin's operand)
+            const uint32_t vo = aoff[v];
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra_rs, (lds_ptr)(sa + (wave_u * AV + v) * 8 * 64), 16, vo,
+                                                     (uint32_t)k0 * 2u, 0, 0);
         }
-        // B: the blocked weights (256-row blocks of 64-deep K steps, 128-byte
-        // rows): load instruction v of wave_r w covers rows (w BV + v) 8 .. +7
-        // of the tile's block, 1 KB in a row; the K step goes in the scalar offset
-        static_assert(BN == WB_ROWS, "a tile's weight rows are one block");
-        const uint32_t bblk = (uint32_t)(L.n0 / BN) * (uint32_t)(K / WB_K) * (uint32_t)(BN * WB_K * 2) +
-                              (uint32_t)(wave_r * BV * 8 + rsub) * (WB_K * 2u);
+    };
+    auto dmaB = [&](__bf16* sb, int k0) {
+#pragma unroll
+        for (int v = 0; v < BV; ++v)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb_rs, (lds_ptr)(sb + (wave_u * BV + v) * 8 * 64), 16,
+                                                     bblk + v * 1024u + (uint32_t)((v & 1) ? gc1 : gc0) * 16u,
+                                                     (uint32_t)k0 * (uint32_t)(BN * 2), 0, BAUX);
+    };
+    // fragment of row (lane_r & 31) of each 32-row block, K chunk 2 ks + lane_r / 32
+    const int arow = (wm_r * WM + (lane_r & 31)) * 64;
+    const int brow = (wn_r * WN + (lane_r & 31)) * 64;
+    bf16x8 af[2][FM], bfm[2][FN];
+    auto fload = [&](const __bf16* sa, const __bf16* sb, int ks, int slot) {
+        const int pos = ((2 * ks + (lane_r >> 5)) ^ ((lane_r >> 1) & 7)) * 8;   // row & 31 = lane_r & 31
+#pragma unroll
+        for (int i = 0; i < FM; ++i) af[slot][i] = *(const bf16x8*)(sa + arow + i * 32 * 64 + pos);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) bfm[slot][j] = *(const bf16x8*)(sb + brow + j * 32 * 64 + pos);
+    };
+    // the first sub-step's fragments after the barrier, in the order the
+    // MFMAs consume them (A0 B0, then B1.., then A1..), each read fenced so
+    // that the first MFMAs wait for their own operands only (the scheduler
+    // had issued B0 and B1 last, so every K tile began by waiting for seven
+    // of the eight reads)
+    auto fload_first = [&](const __bf16* sa, const __bf16* sb) {
+        const int pos = ((lane_r >> 5) ^ ((lane_r >> 1) & 7)) * 8;   // sub-step 0
+        af[0][0] = *(const bf16x8*)(sa + arow + pos);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            bfm[0][j] = *(const bf16x8*)(sb + brow + j * 32 * 64 + pos);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 1; i < FM; ++i) {
+            af[0][i] = *(const bf16x8*)(sa + arow + i * 32 * 64 + pos);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto mfmas = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[slot][i], bfm[slot][j], acc[i][j], 0, 0, 0);
+    };
+    // Each K tile of 64 is four MFMA sub-steps of 16; every sub-step reads
+    // the fragments of the next one.  The buffers are separate LDS arrays
+    // and the loop is unrolled over a pass of six tiles (A cycles over two
+    // buffers, B over three), so that every access names a fixed array and
+    // the loads into one buffer are never taken to alias the reads of
+    // another.  The barrier of K tile t sits before its last sub-step.
+    // Sub-step 0 issues the B loads of tile t + 2 (into the buffer tile
+    // t - 1 read, free since barrier t - 1); after sub-step 2 every fragment
+    // of tile t has been read, so the wave waits for its own loads of tile
+    // t + 1 (everything but the B loads just issued) and its reads, and the
+    // barrier follows; sub-step 3's MFMAs then overlap the first fragment
+    // reads of tile t + 1 and the A loads of tile t + 2 into the A buffer
+    // tile t has just finished with.  The A loads keep a lead of four
+    // sub-steps, the B loads of seven; no tile starts by waiting for its
+    // first fragments.  Loads past the piece re-read its last K tile into
+    // an idle buffer.
+    constexpr int NM = FM * FN, NR = FM + FN;
+    constexpr int VMEM_READ = 0x020;
+    auto ktile = [&](__bf16* ca, __bf16* cb, __bf16* na, __bf16* nbn, __bf16* nbl, int kn2)
+                     __attribute__((always_inline)) {
+        dmaB(nbl, kn2);
+        fload(ca, cb, 1, 1);
+        mfmas(0);
+        sched_interleave<0, NM, NR, BV, VMEM_READ>();
+        __builtin_amdgcn_sched_barrier(0);
+        fload(ca, cb, 2, 0);
+        mfmas(1);
+        sched_interleave<0, NM, NR, 0, VMEM_READ>();
+        __builtin_amdgcn_sched_barrier(0);
+        fload(ca, cb, 3, 1);
+        mfmas(0);
+        sched_interleave<0, NM, NR, 0, VMEM_READ>();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(waitcnt_enc(BV, 0));
+        lds_barrier();
+        dmaA(ca, kn2);
+        fload(na, nbn, 0, 0);
+        mfmas(1);
+        sched_interleave<0, NM, NR, AV, VMEM_READ>();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the piece's K tiles [kt_lo, kt_hi): an even number (K units of 128)
+    const int klast = kt_hi - 1;
+    auto kc = [&](int k) { return (k < kt_hi ? k : klast) * BK; };
+    // buffers of tile kt + u of a pass (compile-time u)
+    auto bufA = [&](auto u) -> __bf16* { return decltype(u)::value % 2 == 0 ? sA0 : sA1; };
+    auto bufB = [&](auto u) -> __bf16* {
+        constexpr int j = decltype(u)::value % 3;
+        if constexpr (j == 0) return sB0; else if constexpr (j == 1) return sB1; else return sB2;
+    };
+    // prologue: tiles kt_lo and kt_lo + 1 of both operands
+    dmaA(sA0, kt_lo * BK);
+    dmaB(sB0, kt_lo * BK);
+    dmaB(sB1, kc(kt_lo + 1));
+    dmaA(sA1, kc(kt_lo + 1));
+    static_assert(AV + BV < 64, "vmcnt field");
+    __builtin_amdgcn_s_waitcnt(waitcnt_enc(AV + BV, 15));   // tile kt_lo's loads are in LDS
+    lds_barrier();
+    fload_first(sA0, sB0);
+    __builtin_amdgcn_sched_barrier(0);
+    auto step = [&](auto u, int kt) __attribute__((always_inline)) {
+        constexpr int U = decltype(u)::value;
+        using N1 = std::integral_constant<int, U + 1>;
+        using N2 = std::integral_constant<int, U + 2>;
+        ktile(bufA(u), bufB(u), bufA(N1{}), bufB(N1{}), bufB(N2{}), kc(kt + U + 2));
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    using I4 = std::integral_constant<int, 4>;
+    using I5 = std::integral_constant<int, 5>;
+    int kt = kt_lo;
+    for (; kt + 6 <= kt_hi; kt += 6) {
+        step(I0{}, kt); step(I1{}, kt); step(I2{}, kt);
+        step(I3{}, kt); step(I4{}, kt); step(I5{}, kt);
+    }
+    // the two or four tiles left start a pass
+    if (kt < kt_hi) {
+        step(I0{}, kt); step(I1{}, kt);
+        if (kt + 2 < kt_hi) { step(I2{}, kt); step(I3{}, kt); }
+    }
+    // loads of the tiles after the last may still be in flight
+    __builtin_amdgcn_s_waitcnt(0x0F70);
 
-        f32x16 acc[FM][FN];
+    if (nseg > 1) {
+        // a piece of a split tile: its partial sums go to slot j sstride + ctr
+        // (its position in the round), thread tid_r's 16-byte group h of
+        // block (i, j) at byte (((i FN + j) 4 + h) 256 + tid_r) 16 of the slot
+        // (each store instruction writes 4 KB in a row).  Buffer stores and loads keep the lane_r's offset in
+        // one register and the slot and group in the scalar offset.  They
+        // carry the sc1 cache bit (the bit of agent-scope atomic loads and
+        // stores), so each location is coherent across the XCDs' L2 caches
+        // without a whole-cache write-back or invalidate, which would also
+        // evict the tiles of every other workgroup on the XCD.  The stores
+        // complete (vmcnt 0) before the arrival is counted, and the last
+        // arrival's loads are issued after the count is read.
+        const __amdgpu_buffer_rsrc_t rp = make_rsrc(p.sk_part, (uint32_t)(SK_MAX_GRID - 1) * 256u * BN * 4u);
+        const uint32_t lo = (uint32_t)tid_r * 16u;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                for (int h = 0; h < 4; ++h) {
+                    const f32x4 v{acc[i][j][4 * h], acc[i][j][4 * h + 1], acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rp, (int)lo,
+                                                           (int)((uint32_t)pslot * slot_bytes +
+                                                                 (uint32_t)((i * FN + j) * 4 + h) * 4096u), SC1);
+                }
+        __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): this wave_r's stores are done
+        __syncthreads();
+        if (tid_r == 0) *s_last = atomicAdd(p.sk_cnt + MODE * SK_MAX_GRID + ctr, 1) == nseg - 1;
+        __syncthreads();
+        if (!*s_last) return;
+        // the last arrival: the tile is the sum of its pieces in K order
+        // (piece j in slot j * sstride + ctr).  Every group reads SK_SPLIT
+        // pieces without a branch, so that the loads of many groups are in
+        // flight together: the pieces past nseg have a lane_r offset past the
+        // buffer (the range check covers the lane_r offset) and read as
+        // zeros, and adding them leaves the sum as it is (up to the sign of
+        // a zero).
+        uint32_t pbase[SK_SPLIT], plo[SK_SPLIT];
+#pragma unroll
+        for (int sg = 0; sg < SK_SPLIT; ++sg) {
+            pbase[sg] = sg < nseg ? (uint32_t)(pslot0 + sg * sstride) * slot_bytes : 0u;
+            plo[sg] = sg < nseg ? lo : OOR;
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const uint32_t go = (uint32_t)((i * FN + j) * 4 + h) * 4096u;
+                    f32x4 pv[SK_SPLIT];
+#pragma unroll
+                    for (int sg = 0; sg < SK_SPLIT; ++sg) {
+                        const uint32_t vo = plo[sg];
+                        pv[sg] = __builtin_bit_cast(
+                            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, (int)vo, (int)(pbase[sg] + go), SC1));
+                    }
+                    f32x4 v = pv[0];
+#pragma unroll
+                    for (int sg = 1; sg < SK_SPLIT; ++sg) v += pv[sg];
+                    acc[i][j][4 * h] = v[0];
+                    acc[i][j][4 * h + 1] = v[1];
+                    acc[i][j][4 * h + 2] = v[2];
+                    acc[i][j][4 * h + 3] = v[3];
+                }
+    }
 
-        // the loads of a K tile go from memory straight into LDS buffer b
-        auto dmaA = [&](__bf16* sa, int k0) {
-#pragma unroll
-            for (int v = 0; v < AV; ++v) {
-                // (a local copy: the host pass drops the kernel when an array
-                // element captured by reference is the builtin's operand)
-                const uint32_t vo = aoff[v];
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra_rs, (lds_ptr)(sa + (wave_u * AV + v) * 8 * 64), 16, vo,
-                                                         (uint32_t)k0 * 2u, 0, 0);
-            }
-        };
-        auto dmaB = [&](__bf16* sb, int k0) {
-#pragma unroll
-            for (int v = 0; v < BV; ++v)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb_rs, (lds_ptr)(sb + (wave_u * BV + v) * 8 * 64), 16,
-                                                         bblk + v * 1024u + (uint32_t)((v & 1) ? gc1 : gc0) * 16u,
-                                                         (uint32_t)k0 * (uint32_t)(BN * 2), 0, 0);
-        };
-        // fragment of row (lane_r & 31) of each 32-row block, K chunk 2 ks + lane_r / 32
-        const int arow = (wm_r * WM + (lane_r & 31)) * 64;
-        const int brow = (wn_r * WN + (lane_r & 31)) * 64;
-        bf16x8 af[2][FM], bfm[2][FN];
-        auto fload = [&](const __bf16* sa, const __bf16* sb, int ks, int slot) {
-            const int pos = ((2 * ks + (lane_r >> 5)) ^ ((lane_r >> 1) & 7)) * 8;   // row & 31 = lane_r & 31
-#pragma unroll
-            for (int i = 0; i < FM; ++i) af[slot][i] = *(const bf16x8*)(sa + arow + i * 32 * 64 + pos);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) bfm[slot][j] = *(const bf16x8*)(sb + brow + j * 32 * 64 + pos);
-        };
-        // the first sub-step's fragments after the barrier, in the order the
-        // MFMAs consume them (A0 B0, then B1.., then A1..), each read fenced so
-        // that the first MFMAs wait for their own operands only (the scheduler
-        // had issued B0 and B1 last, so every K tile began by waiting for seven
-        // of the eight reads)
-        auto fload_first = [&](const __bf16* sa, const __bf16* sb) {
-            const int pos = ((lane_r >> 5) ^ ((lane_r >> 1) & 7)) * 8;   // sub-step 0
-            af[0][0] = *(const bf16x8*)(sa + arow + pos);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                bfm[0][j] = *(const bf16x8*)(sb + brow + j * 32 * 64 + pos);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int i = 1; i < FM; ++i) {
-                af[0][i] = *(const bf16x8*)(sa + arow + i * 32 * 64 + pos);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        auto mfmas = [&](int slot) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[slot][i], bfm[slot][j], acc[i][j], 0, 0, 0);
-        };
-        // Each K tile of 64 is four MFMA sub-steps of 16; every sub-step reads
-        // the fragments of the next one.  The buffers are separate LDS arrays
-        // and the loop is unrolled over a pass of six tiles (A cycles over two
-        // buffers, B over three), so that every access names a fixed array and
-        // the loads into one buffer are never taken to alias the reads of
-        // another.  The barrier of K tile t sits before its last sub-step.
-        // Sub-step 0 issues the B loads of tile t + 2 (into the buffer tile
-        // t - 1 read, free since barrier t - 1); after sub-step 2 every fragment
-        // of tile t has been read, so the wave waits for its own loads of tile
-        // t + 1 (everything but the B loads just issued) and its reads, and the
-        // barrier follows; sub-step 3's MFMAs then overlap the first fragment
-        // reads of tile t + 1 and the A loads of tile t + 2 into the A buffer
-        // tile t has just finished with.  The A loads keep a lead of four
-        // sub-steps, the B loads of seven; no tile starts by waiting for its
-        // first fragments.  Loads past the piece re-read its last K tile into
-        // an idle buffer.
-        constexpr int NM = FM * FN, NR = FM + FN;
-        constexpr int VMEM_READ = 0x020;
-        auto ktile = [&](__bf16* ca, __bf16* cb, __bf16* na, __bf16* nbn, __bf16* nbl, int kn2)
-                         __attribute__((always_inline)) {
-            dmaB(nbl, kn2);
-            fload(ca, cb, 1, 1);
-            mfmas(0);
-            sched_interleave<0, NM, NR, BV, VMEM_READ>();
-            __builtin_amdgcn_sched_barrier(0);
-            fload(ca, cb, 2, 0);
-            mfmas(1);
-            sched_interleave<0, NM, NR, 0, VMEM_READ>();
-            __builtin_amdgcn_sched_barrier(0);
-            fload(ca, cb, 3, 1);
-            mfmas(0);
-            sched_interleave<0, NM, NR, 0, VMEM_READ>();
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(waitcnt_enc(BV, 0));
-            lds_barrier();
-            dmaA(ca, kn2);
-            fload(na, nbn, 0, 0);
-            mfmas(1);
-            sched_interleave<0, NM, NR, AV, VMEM_READ>();
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        // the piece's K tiles [kt_lo, kt_hi): an even number (K units of 128)
-        const int klast = kt_hi - 1;
-        auto kc = [&](int k) { return (k < kt_hi ? k : klast) * BK; };
-        // buffers of tile kt + u of a pass (compile-time u)
-        auto bufA = [&](auto u) -> __bf16* { return decltype(u)::value % 2 == 0 ? sA0 : sA1; };
-        auto bufB = [&](auto u) -> __bf16* {
-            constexpr int j = decltype(u)::value % 3;
-            if constexpr (j == 0) return sB0; else if constexpr (j == 1) return sB1; else return sB2;
-        };
-        // prologue: tiles kt_lo and kt_lo + 1 of both operands
-        dmaA(sA0, kt_lo * BK);
-        dmaB(sB0, kt_lo * BK);
-        dmaB(sB1, kc(kt_lo + 1));
-        dmaA(sA1, kc(kt_lo + 1));
-        static_assert(AV + BV < 64, "vmcnt field");
-        __builtin_amdgcn_s_waitcnt(waitcnt_enc(AV + BV, 15));   // tile kt_lo's loads are in LDS
+    // epilogue: element e of a 32x32 block is row (e/4)*8 + (lane_r/32)*4 + e%4,
+    // column lane_r%32.  Down scales each row by its gate weight, parked in
+    // LDS by the workgroup (the barrier also orders it after the previous
+    // tile's reads, which precede this tile's K-loop barriers).
+    if constexpr (MODE == 1) {
+        // (in sB2: after every wave's last fragment reads of the K loop)
         lds_barrier();
-        fload_first(sA0, sB0);
-        __builtin_amdgcn_sched_barrier(0);
-        auto step = [&](auto u, int kt) __attribute__((always_inline)) {
-            constexpr int U = decltype(u)::value;
-            using N1 = std::integral_constant<int, U + 1>;
-            using N2 = std::integral_constant<int, U + 2>;
-            ktile(bufA(u), bufB(u), bufA(N1{}), bufB(N1{}), bufB(N2{}), kc(kt + U + 2));
-        };
-        using I0 = std::integral_constant<int, 0>;
-        using I1 = std::integral_constant<int, 1>;
-        using I2 = std::integral_constant<int, 2>;
-        using I3 = std::integral_constant<int, 3>;
-        using I4 = std::integral_constant<int, 4>;
-        using I5 = std::integral_constant<int, 5>;
-        int kt = kt_lo;
-        for (; kt + 6 <= kt_hi; kt += 6) {
-            step(I0{}, kt); step(I1{}, kt); step(I2{}, kt);
-            step(I3{}, kt); step(I4{}, kt); step(I5{}, kt);
-        }
-        // the two or four tiles left start a pass
-        if (kt < kt_hi) {
-            step(I0{}, kt); step(I1{}, kt);
-            if (kt + 2 < kt_hi) { step(I2{}, kt); step(I3{}, kt); }
-        }
-        // loads of the tiles after the last may still be in flight
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-
-        if (nseg > 1) {
-            // a piece of a split tile: its partial sums go to slot j sstride + ctr
-            // (its position in the round), thread tid_r's 16-byte group h of
-            // block (i, j) at byte (((i FN + j) 4 + h) 256 + tid_r) 16 of the slot
-            // (each store instruction writes 4 KB in a row).  Buffer stores and loads keep the lane_r's offset in
-            // one register and the slot and group in the scalar offset.  They
-            // carry the sc1 cache bit (the bit of agent-scope atomic loads and
-            // stores), so each location is coherent across the XCDs' L2 caches
-            // without a whole-cache write-back or invalidate, which would also
-            // evict the tiles of every other workgroup on the XCD.  The stores
-            // complete (vmcnt 0) before the arrival is counted, and the last
-            // arrival's loads are issued after the count is read.
-            constexpr uint32_t TILE_BYTES = (uint32_t)BM * BN * 4u;
-            const __amdgpu_buffer_rsrc_t rp = make_rsrc(p.sk_part, (uint32_t)SK_MAX_GRID * TILE_BYTES);
-            const uint32_t lo = (uint32_t)tid_r * 16u;
+        if (tid_r < BM) s_roww[tid_r] = roww;
+        lds_barrier();
+    }
+    const int rbase = L.m0 + wm_r * WM + (lane_r >> 5) * 4;
+    if constexpr (MODE == 0) {
+        __bf16* out = shared ? (__bf16*)p.Os : (__bf16*)p.Or;
+        const int ldo = L.N / 2;
+        const int orow0 = shared ? 0 : L.rowbase;
+        const int cbase = (L.n0 + wn_r * WN) / 2 + (lane_r & 31);
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
+            for (int e = 0; e < 16; ++e) {
+                const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3);
+                if (row < L.R) {
 #pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        const f32x4 v{acc[i][j][4 * h], acc[i][j][4 * h + 1], acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]};
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rp, (int)lo,
-                                                               (int)((uint32_t)pslot * TILE_BYTES +
-                                                                     (uint32_t)((i * FN + j) * 4 + h) * 4096u), SC1);
+                    for (int q = 0; q < FN / 2; ++q) {
+                        const float gv = acc[i][2 * q][e], uv = acc[i][2 * q + 1][e];
+                        out[(size_t)(orow0 + row) * ldo + cbase + q * 32] = (__bf16)(silu_f(gv) * uv);
                     }
-            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): this wave_r's stores are done
-            __syncthreads();
-            if (tid_r == 0) *s_last = atomicAdd(p.sk_cnt + MODE * SK_MAX_GRID + ctr, 1) == nseg - 1;
-            __syncthreads();
-            if (!*s_last) continue;
-            // the last arrival: the tile is the sum of its pieces in K order
-            // (piece j in slot j * sstride + ctr).  Every group reads SK_SPLIT
-            // pieces without a branch, so that the loads of many groups are in
-            // flight together: the pieces past nseg have a lane_r offset past the
-            // buffer (the range check covers the lane_r offset) and read as
-            // zeros, and adding them leaves the sum as it is (up to the sign of
-            // a zero).
-            uint32_t pbase[SK_SPLIT], plo[SK_SPLIT];
-#pragma unroll
-            for (int sg = 0; sg < SK_SPLIT; ++sg) {
-                pbase[sg] = sg < nseg ? (uint32_t)(ctr + sg * sstride) * TILE_BYTES : 0u;
-                plo[sg] = sg < nseg ? lo : OOR;
+                }
             }
+    } else {
+        __bf16* out = (__bf16*)p.Or;
+        const int ldo = L.N;
+        const int cbase = L.n0 + wn_r * WN + (lane_r & 31);
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
+            for (int e = 0; e < 16; ++e) {
+                const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3);
+                const float wr = s_roww[row - L.m0];
+                if (row < L.R) {
 #pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        const uint32_t go = (uint32_t)((i * FN + j) * 4 + h) * 4096u;
-                        f32x4 pv[SK_SPLIT];
-#pragma unroll
-                        for (int sg = 0; sg < SK_SPLIT; ++sg) {
-                            const uint32_t vo = plo[sg];
-                            pv[sg] = __builtin_bit_cast(
-                                f32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, (int)vo, (int)(pbase[sg] + go), SC1));
-                        }
-                        f32x4 v = pv[0];
-#pragma unroll
-                        for (int sg = 1; sg < SK_SPLIT; ++sg) v += pv[sg];
-                        acc[i][j][4 * h] = v[0];
-                        acc[i][j][4 * h + 1] = v[1];
-                        acc[i][j][4 * h + 2] = v[2];
-                        acc[i][j][4 * h + 3] = v[3];
-                    }
-        }
+                    for (int j = 0; j < FN; ++j)
+                        out[(size_t)(L.rowbase + row) * ldo + cbase + j * 32] = (__bf16)(acc[i][j][e] * wr);
+                }
+            }
+    }
+}
 
-        // epilogue: element e of a 32x32 block is row (e/4)*8 + (lane_r/32)*4 + e%4,
-        // column lane_r%32.  Down scales each row by its gate weight, parked in
-        // LDS by the workgroup (the barrier also orders it after the previous
-        // tile's reads, which precede this tile's K-loop barriers).
-        if constexpr (MODE == 1) {
-            // (in sB2: after every wave's last fragment reads of the K loop)
-            if constexpr (ROWW_IN_SB2) lds_barrier();
-            if (tid_r < BM) s_roww[tid_r] = roww;
-            lds_barrier();
+// The persistent kernel: every workgroup walks the published work list, whole
+// rounds of items in snake order (odd rounds reversed), then the items left
+// over, cut along K where the list says so.  What bounds it is the weight stream
+// (few rows per expert) or the MFMA rate at the card's power limit (many).  Tile
+// heights follow the row counts: with 256-row (down: 192) tiles alone an expert
+// of 12 rows cost as much as one of 256.  Gate/up, down before and now: 8 experts
+// of 77 rows and 512 shared rows of d = 2048, f = 1408: 49 and 48 -> 40 and 30 us;
+// 15 of 12 and 126 shared: 51 and 65 -> 44 and 35; 32 of 43 rows of d = 4096,
+// f = 1536: 178 and 94 -> 132 and 82; 2 of 1119 of d = 4096, f = 14336: even.
+template <int MODE>
+__global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
+    __shared__ __attribute__((aligned(16))) __bf16 sA0[256 * 64], sA1[256 * 64], sB0[TP_BN * 64], sB1[TP_BN * 64];
+    __shared__ __attribute__((aligned(16))) __bf16 sB2[TP_BN * 64];
+    const TilePlan* P = p.plan;
+    const int grid = (int)gridDim.x;                // a multiple of 8, at most SK_MAX_GRID
+    const int vid = (blockIdx.x & 7) * (grid >> 3) + (blockIdx.x >> 3);
+    const int H = P->H, rounds = P->rounds, items = P->items, sp0 = P->sp0, split = P->split, q = P->q, nsh = P->nsh;
+    const bool spread = P->spread != 0;
+    const uint32_t slot_bytes = (uint32_t)H * 64u * TP_BN * 4u;
+    const int head = rounds * grid, whole = sp0 - head, ns = items - sp0;
+    const TileSeg Ssh = P->seg[p.n_routed];         // the shared group
+    for (int r = 0; r <= rounds; ++r) {
+        // lane g reads routed group g's segment (again for every tile: held across the
+        // K loop it would spill), beside the reads of the list's head
+        const int lane = threadIdx.x & 63, n = p.n_routed;
+        const TileSeg V = P->seg[lane < n ? lane : n];
+        const int pos = round_pos(vid, r, r < rounds ? grid : whole + split * ns, grid, spread);
+        if (pos < 0) break;
+        int item = r * grid + pos, lj = 0;
+        const bool cut = r == rounds && split > 1 && pos >= whole;
+        if (cut) {
+            lj = (pos - whole) / ns;                             // K piece of a left-over item
+            item = sp0 + (pos - whole) - lj * ns;
         }
-        const int rbase = L.m0 + wm_r * WM + (lane_r >> 5) * 4;
+        // the group of the item: the last one that starts at or before it (an empty group
+        // starts where the next one does)
+        const bool shared = item < nsh * q;
+        int g = n, mt_hl = Ssh.mt_hl, t = item - Ssh.first;
+        TileLoc L;
+        L.R = Ssh.R;
+        L.rowbase = Ssh.off;
+        if (!shared) {
+            g = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(lane < n && V.first <= item));
+            mt_hl = __builtin_amdgcn_readlane(V.mt_hl, g);
+            t = item - __builtin_amdgcn_readlane(V.first, g);
+            L.R = __builtin_amdgcn_readlane(V.R, g);
+            L.rowbase = __builtin_amdgcn_readlane(V.off, g);
+        }
+        L.g = g;
+        L.N = shared ? p.Ns : p.Nr;
+        L.K = shared ? p.Ks : p.Kr;
+        const int mt = mt_hl >> 3;
+        const int units = L.K / 128;                             // K in steps of two K tiles
+        int kt_lo = 0, kt_hi = 2 * units, nseg = 1, ctr = 0, pslot = 0, pslot0 = 0, sstride = 0;
+        if (shared && q > 1) {
+            const int j = t / nsh;
+            t -= j * nsh;
+            nseg = q;
+            ctr = pslot0 = t;
+            sstride = nsh;
+            pslot = t + j * nsh;
+            kt_lo = 2 * (j * units / q);
+            kt_hi = 2 * ((j + 1) * units / q);
+        } else if (cut) {
+            // (shared pieces have the first slots and counters)
+            nseg = split;
+            ctr = (q > 1 ? nsh : 0) + item - sp0;
+            sstride = ns;
+            pslot0 = (q > 1 ? nsh * q : 0) + item - sp0;
+            pslot = pslot0 + lj * ns;
+            kt_lo = 2 * (lj * units / split);
+            kt_hi = 2 * ((lj + 1) * units / split);
+        }
+        const int ni = t / mt, mi = t - ni * mt;
+        L.n0 = ni * TP_BN;
+        L.m0 = mi * H * 64;
+        const int h = mi == mt - 1 ? mt_hl & 7 : H;
         if constexpr (MODE == 0) {
-            __bf16* out = shared ? (__bf16*)p.Os : (__bf16*)p.Or;
-            const int ldo = L.N / 2;
-            const int orow0 = shared ? 0 : L.rowbase;
-            const int cbase = (L.n0 + wn_r * WN) / 2 + (lane_r & 31);
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3);
-                    if (row < L.R) {
-#pragma unroll
-                        for (int q = 0; q < FN / 2; ++q) {
-                            const float gv = acc[i][2 * q][e], uv = acc[i][2 * q + 1][e];
-                            out[(size_t)(orow0 + row) * ldo + cbase + q * 32] = (__bf16)(silu_f(gv) * uv);
-                        }
-                    }
-                }
-        } else {
-            __bf16* out = (__bf16*)p.Or;
-            const int ldo = L.N;
-            const int cbase = L.n0 + wn_r * WN + (lane_r & 31);
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3);
-                    const float wr = s_roww[row - L.m0];
-                    if (row < L.R) {
-#pragma unroll
-                        for (int j = 0; j < FN; ++j)
-                            out[(size_t)(L.rowbase + row) * ldo + cbase + j * 32] = (__bf16)(acc[i][j][e] * wr);
-                    }
-                }
+            // weights that one short row tile reads, of a layer that outgrows the
+            // caches: non-temporal, as in the thin GEMM (GemmArgs::stream)
+            if (p.stream && mt == 1 && h <= 2) {
+                if (h == 2) bf16_tile<128, MODE, NT>(p, L, kt_lo, kt_hi, nseg, ctr, pslot, pslot0, sstride, slot_bytes, sA0, sA1, sB0, sB1, sB2);
+                else bf16_tile<64, MODE, NT>(p, L, kt_lo, kt_hi, nseg, ctr, pslot, pslot0, sstride, slot_bytes, sA0, sA1, sB0, sB1, sB2);
+                continue;
+            }
         }
+        if (h == 4) bf16_tile<256, MODE>(p, L, kt_lo, kt_hi, nseg, ctr, pslot, pslot0, sstride, slot_bytes, sA0, sA1, sB0, sB1, sB2);
+        else if (h == 3) bf16_tile<192, MODE>(p, L, kt_lo, kt_hi, nseg, ctr, pslot, pslot0, sstride, slot_bytes, sA0, sA1, sB0, sB1, sB2);
+        else if (h == 2) bf16_tile<128, MODE>(p, L, kt_lo, kt_hi, nseg, ctr, pslot, pslot0, sstride, slot_bytes, sA0, sA1, sB0, sB1, sB2);
+        else bf16_tile<64, MODE>(p, L, kt_lo, kt_hi, nseg, ctr, pslot, pslot0, sstride, slot_bytes, sA0, sA1, sB0, sB1, sB2);
     }
 }
 
@@ -1377,17 +1591,16 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 }
 
 
-constexpr int GU_BM = 256, GU_BN = 256, DN_BM = 192, DN_BN = 256;   // bf16 GEMM tiles
-// Large batches take 256-row down tiles: when even 256-row tiles would fill
-// the grid DN_TALL_ROUNDS times over by the host's upper bound on the rows,
-// the taller tile's better operand reuse outweighs the rounding of the last
-// tile of each group and the shorter last round; smaller batches keep 192
-// rows, which spread a few thousand rows over more of the 256 CUs.
-constexpr int DN_BM_TALL = 256;
-constexpr int64_t DN_TALL_ROUNDS = 8;
 // bf16 batches of at most THIN_MAX_T tokens (every expert then has at most that
 // many rows) take the thin GEMM, THIN_PER_CU resident workgroups per CU
 constexpr int64_t THIN_MAX_T = 128;
+// Routed gate/up weights of at least this many bytes are streamed by short single
+// row tiles with non-temporal loads: 805 MB (32 experts of d = 4096, f = 1536)
+// 148 -> 131 us, 92 MB (8 of d = 2048, f = 1408) 53 -> 49 us; smaller ones are
+// found in the caches by the next call, which such loads forfeit: 21 MB (8 of
+// d = 1024, f = 640) 15 -> 19 us.  (In the down GEMM the further tile variants
+// spilled: 78 -> 85 us at the first shape; it keeps ordinary loads.)
+constexpr int64_t STREAM_BYTES = 64 << 20;
 constexpr int THIN_PER_CU = 3;
 
 int persistent_grid(int64_t upper_tiles, int per_cu) {
@@ -1415,8 +1628,8 @@ size_t forward_split_counters() { return 2 * SK_MAX_GRID; }
 
 size_t forward_split_floats(int dtype, int64_t T) {
     if (dtype != ORDERMOE_BF16 || forward_uses_thin(dtype, T)) return 0;
-    const size_t tile = (size_t)GU_BM * GU_BN > (size_t)DN_BM * DN_BN ? (size_t)GU_BM * GU_BN : (size_t)DN_BM * DN_BN;
-    return (size_t)SK_MAX_GRID * tile;
+    static_assert(2 * sizeof(TilePlan) <= 256 * TP_BN * sizeof(float), "the work lists fit the last slot");
+    return (size_t)SK_MAX_GRID * 256 * TP_BN;
 }
 
 int forward_tokens_per_block() { return FT_TB; }
@@ -1425,7 +1638,7 @@ bool forward_uses_thin(int dtype, int64_t T) { return dtype == ORDERMOE_BF16 && 
 
 void forward_tile_shape(int dtype, int64_t T, int* bm_gu, int* bn_gu, int* bm_dn, int* bn_dn) {
     if (forward_uses_thin(dtype, T)) { *bm_gu = *bm_dn = TH_BM; *bn_gu = *bn_dn = TH_BN; }
-    else if (dtype == ORDERMOE_BF16) { *bm_gu = GU_BM; *bn_gu = GU_BN; *bm_dn = DN_BM; *bn_dn = DN_BN; }
+    else if (dtype == ORDERMOE_BF16) { *bm_gu = *bm_dn = 64; *bn_gu = *bn_dn = TP_BN; }   // (the shortest tile)
     else { *bm_gu = F32_BM; *bn_gu = F32_BN; *bm_dn = F32_BM; *bn_dn = F32_BN; }
 }
 
@@ -1437,9 +1650,12 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     int bm_gu, bn_gu, bm_dn, bn_dn;
     forward_tile_shape(f.dtype, f.T, &bm_gu, &bn_gu, &bm_dn, &bn_dn);
     const int64_t rows_r = f.rmax_routed, rows_s = has_sh ? f.T : 0;
-    if (!thin && f.dtype == ORDERMOE_BF16 &&
-        ((rows_r + rows_s + DN_BM_TALL - 1) / DN_BM_TALL + G) * (f.d / DN_BN) >= DN_TALL_ROUNDS * SK_MAX_GRID)
-        bm_dn = DN_BM_TALL;
+    // upper bounds of the tiles, for the grids
+    const int64_t ub_gu = ((rows_r + bm_gu - 1) / bm_gu + f.n_local) * (2 * f.f / bn_gu) +
+                          (has_sh ? ((rows_s + bm_gu - 1) / bm_gu + 1) * (2 * f.n_shared * f.f / bn_gu) : 0);
+    const int64_t ub_dn = ((rows_r + rows_s + bm_dn - 1) / bm_dn + G) * (f.d / bn_dn);
+    const bool tiled = !thin && f.dtype == ORDERMOE_BF16;
+    TilePlan* plan = tiled ? (TilePlan*)(f.sk_part + (size_t)(SK_MAX_GRID - 1) * 256 * TP_BN) : nullptr;
 
     RowsArgs r;
     r.T = f.T; r.k = f.k; r.E = f.E; r.n_local = f.n_local; r.has_shared = has_sh; r.server = f.server;
@@ -1450,6 +1666,17 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     r.sk_cnt = f.sk_cnt; r.nblk = f.nblk;
     r.bm_gu = bm_gu; r.bn_gu = bn_gu; r.bm_dn = bm_dn; r.bn_dn = bn_dn;
     r.n_gu_r = 2 * f.f; r.n_gu_s = 2 * f.n_shared * f.f; r.n_dn = f.d;
+    r.plan = plan;
+    for (int w = 0; w < 2; ++w) {
+        PlanShape& c = r.shape[w];
+        c.nt_r = (w == 0 ? r.n_gu_r : r.n_dn) / TP_BN;
+        c.nt_s = (w == 0 ? r.n_gu_s : r.n_dn) / TP_BN;
+        c.kt_r = (w == 0 ? f.d : f.f) / 64;
+        c.kt_s = (w == 0 ? f.d : f.n_shared * f.f) / 64;
+        c.q = has_sh && c.kt_s >= 2 * c.kt_r ? (c.kt_s / c.kt_r < SK_SPLIT ? c.kt_s / c.kt_r : SK_SPLIT) : 1;
+        c.grid = bf16_grid(w == 0 ? ub_gu : ub_dn);
+        c.grid_inv = (uint32_t)(((1ull << 32) + c.grid - 1) / c.grid);
+    }
 
     hipError_t e;
     if (f.T <= SCAN_THREADS) {
@@ -1467,7 +1694,7 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
         if ((e = hipGetLastError()) != hipSuccess) return (int)e;
         {
             KernelTimer kt_("rows_scatter", st);
-            hipLaunchKernelGGL(rows_scatter_kernel, dim3(f.nblk), dim3(FT_TB), 0, st, r);
+            hipLaunchKernelGGL(rows_scatter_kernel, dim3(f.nblk + (plan ? 1 : 0)), dim3(FT_TB), 0, st, r);
         }
         if ((e = hipGetLastError()) != hipSuccess) return (int)e;
     }
@@ -1482,10 +1709,6 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     g.ntiles = f.tile_info + 0;
     g.Nr = 2 * f.f; g.Kr = f.d; g.Ns = 2 * f.n_shared * f.f; g.Ks = f.d;
     g.Wr = f.w_gu; g.Ws = f.w_sh_gu; g.Ar = nullptr; g.As = nullptr; g.Or = f.act_r; g.Os = f.act_s;
-    int64_t ub_gu = ((rows_r + bm_gu - 1) / bm_gu + f.n_local) * (2 * f.f / bn_gu) +
-                    (has_sh ? ((rows_s + bm_gu - 1) / bm_gu + 1) * (2 * f.n_shared * f.f / bn_gu) : 0);
-    int64_t ub_dn = ((rows_r + rows_s + bm_dn - 1) / bm_dn + G) * (f.d / bn_dn);
-
     if (thin) {
         {
         KernelTimer kt_("gemm_gate_up", st);
@@ -1495,7 +1718,9 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     } else if (f.dtype == ORDERMOE_BF16) {
         {
         KernelTimer kt_("gemm_gate_up", st);
-        ggemm_bf16<GU_BM, GU_BN, 0><<<dim3(bf16_grid(ub_gu)), dim3(256), 0, st>>>(g);
+        g.plan = plan;
+        g.stream = (int64_t)f.n_local * 2 * f.f * f.d * 2 >= STREAM_BYTES;
+        ggemm_bf16<0><<<dim3(r.shape[0].grid), dim3(256), 0, st>>>(g);
         }
         if ((e = hipGetLastError()) != hipSuccess) return (int)e;
     } else {
@@ -1518,8 +1743,8 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     } else if (f.dtype == ORDERMOE_BF16) {
         {
         KernelTimer kt_("gemm_down", st);
-        if (bm_dn == DN_BM_TALL) ggemm_bf16<DN_BM_TALL, DN_BN, 1><<<dim3(bf16_grid(ub_dn)), dim3(256), 0, st>>>(g);
-        else ggemm_bf16<DN_BM, DN_BN, 1><<<dim3(bf16_grid(ub_dn)), dim3(256), 0, st>>>(g);
+        g.plan = plan + 1;
+        ggemm_bf16<1><<<dim3(r.shape[1].grid), dim3(256), 0, st>>>(g);
         }
     } else {
         {

@@ -1,0 +1,79 @@
+"""The bf16 tiled forward (batches above 128 tokens) where its work list can go
+wrong: row counts at the edges of the 64-row units and of the tile heights,
+empty groups, shared tiles cut into K pieces beside whole routed tiles, several
+rounds of the grid with pieces left over.  Against fp64, through the C ABI."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2607_17154_amd import ordermoe as om  # noqa: E402
+
+
+@pytest.mark.parametrize("rows,d,f,n_shared,here", [
+    ([129], 256, 128, 0, 0),                            # the smallest matrices: one column tile, 2 K tiles
+    ([63, 64, 65, 1, 0, 128, 129], 256, 256, 0, 0),     # unit edges, an empty group between others
+    ([192, 193, 255, 256, 257, 0], 512, 384, 1, 130),   # height edges, the last group empty, shared K = routed K
+    ([0, 40, 300], 512, 256, 4, 321),                   # shared K four times the routed K: four pieces
+    ([700, 20, 513], 2048, 1024, 2, 900),               # long K: pieces of shared and of left-over tiles
+    ([5000, 300, 4000, 33], 512, 2048, 2, 3000),        # several rounds in both GEMMs, ragged ends
+    ([20] * 64, 256, 128, 1, 1280),                     # as many groups as fit, all in 64-row tiles
+])
+def test_bf16_forward_at_the_tile_edges(rows, d, f, n_shared, here):
+    """Rows per expert as listed, one slot per token; the first `here` tokens also
+    run the shared expert.  Three roundings to bf16 (activation, row output, y),
+    each 2^-9 relative to values of the output's scale, spread over the sums:
+    8 x 2^-9 of the largest output bounds them with room; two runs are equal."""
+    rng = np.random.default_rng(sum(rows) + d)
+    n, T = len(rows), int(sum(rows))
+    bf = torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + f)
+    mk = lambda *s: (torch.randn(*s, generator=g, device="cuda") * s[-1] ** -0.5).to(bf)  # noqa: E731
+    x = torch.randn(T, d, generator=g, device="cuda").to(bf)
+    wt = torch.rand(T, 1, generator=g, device="cuda") + 0.25
+    ek = torch.from_numpy(rng.permutation(np.repeat(np.arange(n), rows)).astype(np.int32)).cuda().view(T, 1)
+    loc = torch.from_numpy((np.arange(T) >= here).astype(np.uint8)).cuda()      # 0: the shared expert runs
+    wg, wu, wd = mk(n, f, d), mk(n, f, d), mk(n, d, f)
+    gu, dn = torch.empty((n, 2 * f, d), dtype=bf, device="cuda"), torch.empty_like(wd)
+    om.ordermoe_pack_gate_up(wg, wu, gu)
+    om.ordermoe_pack_down(wd, dn)
+    sgu = sdn = None
+    if n_shared:
+        sg, su, sd = mk(1, n_shared * f, d), mk(1, n_shared * f, d), mk(1, d, n_shared * f)
+        sgu, sdn = torch.empty((1, 2 * n_shared * f, d), dtype=bf, device="cuda"), torch.empty_like(sd)
+        om.ordermoe_pack_gate_up(sg, su, sgu)
+        om.ordermoe_pack_down(sd, sdn)
+    ex = om.make_experts(om.BF16, d, f, n, list(range(n)), gu, dn, n_shared, sgu, sdn)
+    ro = torch.empty(n + 2, dtype=torch.int32, device="cuda")
+    ws = torch.empty(om.ordermoe_forward_workspace_size(ex, T, 1), dtype=torch.uint8, device="cuda")
+    m = torch.zeros((T, 1), dtype=torch.uint8, device="cuda")
+    ys = []
+    for _ in range(2):
+        ws.fill_(255)                                   # nothing of an earlier call is relied on
+        y = torch.empty((T, d), dtype=bf, device="cuda")
+        om.ordermoe_local_moe_forward(ex, x, T, 1, wt, ek, m, loc, 0, y, ro, ws)
+        torch.cuda.synchronize()
+        ys.append(y)
+    assert torch.equal(ys[0], ys[1])
+
+    def ffn(xs, a, b, c):
+        h = xs @ a.double().t().contiguous()
+        return (h / (1 + torch.exp(-h)) * (xs @ b.double().t().contiguous())) @ c.double().t().contiguous()
+
+    xd = x.double()
+    want = torch.zeros_like(xd)
+    for e in range(n):
+        at = torch.nonzero(ek[:, 0] == e).flatten()
+        if at.numel():
+            want[at] += wt[at].double() * ffn(xd[at], wg[e], wu[e], wd[e])
+    if n_shared:
+        want[:here] += ffn(xd[:here], sg[0], su[0], sd[0])
+    err = ((ys[0].double() - want).abs().amax() / want.abs().amax()).item()
+    print("rows %s d %d f %d: max err %.3g of the largest output" % (rows[:8], d, f, err), flush=True)
+    assert err <= 8 * 2.0 ** -9
+    assert ro.cpu().tolist()[:n] == list(np.concatenate([[0], np.cumsum(rows)[:-1]]))
