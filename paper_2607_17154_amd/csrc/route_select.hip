@@ -11,8 +11,9 @@
 //             row group split over its waves, partial sums added in wave order;
 //       fp32: v_mfma_f64_16x16x4_f64 (exact products, fp64 sums), rounded once
 //             to fp32;
-//   * per token (16 lanes, one DPP row): top-(k+1) by a 64-bit (logit, -index)
-//     key max-reduced over the row with DPP rotations, gates, margin and flag;
+//   * per token (16 lanes, one DPP row): top-(k+1) by the largest logit, then the
+//     lowest index that has it, each reduced over the row with DPP rotations,
+//     gates, margin and flag;
 //   * per slot in rank order: the candidate search of eq (40)/(43) -- lane 0
 //     takes the exact candidate, lane j the (j-1)-th substitute of the LDS-
 //     staged table; each lane scans the servers holding its expert and keeps a
@@ -59,8 +60,8 @@ __device__ inline float ord2f(uint32_t o) {
 
 // Reductions over each row of 16 lanes (one token's lanes) with DPP row
 // rotations by 8, 4, 2, 1: after the four steps every lane of the row holds
-// the result.  Max and min are exact in any order; the float sum is used by
-// lane 0 of the row only.
+// the result.  Max and min are exact in any order; of a float sum of several
+// terms only lane 0's is used.
 template <int CTRL>
 __device__ inline uint32_t dpp_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
@@ -71,12 +72,20 @@ __device__ inline uint64_t dpp_u64(uint64_t v) {
     return ((uint64_t)hi << 32) | lo;
 }
 constexpr int DPP_ROR8 = 0x128, DPP_ROR4 = 0x124, DPP_ROR2 = 0x122, DPP_ROR1 = 0x121;
-__device__ inline uint64_t row_max_u64(uint64_t v) {
-    uint64_t o;
-    o = dpp_u64<DPP_ROR8>(v); v = o > v ? o : v;
-    o = dpp_u64<DPP_ROR4>(v); v = o > v ? o : v;
-    o = dpp_u64<DPP_ROR2>(v); v = o > v ? o : v;
-    o = dpp_u64<DPP_ROR1>(v); v = o > v ? o : v;
+__device__ inline uint32_t row_max_u32(uint32_t v) {
+    uint32_t o;
+    o = dpp_u32<DPP_ROR8>(v); v = o > v ? o : v;
+    o = dpp_u32<DPP_ROR4>(v); v = o > v ? o : v;
+    o = dpp_u32<DPP_ROR2>(v); v = o > v ? o : v;
+    o = dpp_u32<DPP_ROR1>(v); v = o > v ? o : v;
+    return v;
+}
+__device__ inline uint32_t row_min_u32(uint32_t v) {
+    uint32_t o;
+    o = dpp_u32<DPP_ROR8>(v); v = o < v ? o : v;
+    o = dpp_u32<DPP_ROR4>(v); v = o < v ? o : v;
+    o = dpp_u32<DPP_ROR2>(v); v = o < v ? o : v;
+    o = dpp_u32<DPP_ROR1>(v); v = o < v ? o : v;
     return v;
 }
 __device__ inline uint64_t row_min_u64(uint64_t v) {
@@ -461,28 +470,33 @@ route_select_kernel(const RouteArgs a) {
         // slices of an element are issued before the additions)
         // PU elements per round: one round of 16-token blocks up to 128
         // experts (up to 64 with two, within the 128 registers of those
-        // kernels); reads past the slices or the batch re-read the first
-        // partial (discarded), so that no branch separates the reads
-        constexpr int PU = NBT >= 8 ? 4 : 2;
-        for (int i0 = tid; i0 < TB * Epad; i0 += PU * RT_THREADS) {
+        // kernels); reads past the slices or the batch lie past the buffer and
+        // return zeros, so that no branch separates the reads
+        // (elements are numbered with NBT * 16 experts per token, so that token and
+        // expert are shifts; a slice's offset goes in the scalar operand)
+        constexpr int PU = NBT >= 8 ? 4 : 2, EP = NBT * 16;
+        const uint32_t sl = (uint32_t)(a.T * Epad) * 4u;          // bytes of a slice: at most 1 MB
+        const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.logit_part, sl * (uint32_t)a.ksplit);
+        for (int i0 = tid; i0 < TB * EP; i0 += PU * RT_THREADS) {
             float pv[PU][RT_SPLIT_MAX_K];
 #pragma unroll
             for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * RT_THREADS;
-                const int64_t tok = t0 + i / Epad;
-                const bool ok = i < TB * Epad && tok < a.T;
+                const int i = i0 + u * RT_THREADS, tr = i / EP, e = i % EP;
+                const bool ok = i < TB * EP && e < Epad && t0 + tr < a.T;
+                const uint32_t vo = ok ? (uint32_t)((t0 + tr) * Epad + e) * 4u : RT_OOR;
 #pragma unroll
                 for (int z = 0; z < RT_SPLIT_MAX_K; ++z)
-                    pv[u][z] = a.logit_part[(z < a.ksplit && ok) ? ((int64_t)z * a.T + tok) * Epad + i % Epad : 0];
+                    pv[u][z] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        rl, (int)(z < a.ksplit ? vo : RT_OOR), (int)(z < a.ksplit ? z * sl : 0u), 0));
             }
 #pragma unroll
             for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * RT_THREADS;
+                const int i = i0 + u * RT_THREADS, tr = i / EP, e = i % EP;
                 float v = 0.f;
 #pragma unroll
                 for (int z = 0; z < RT_SPLIT_MAX_K; ++z)
                     if (z < a.ksplit) v += pv[u][z];
-                if (i < TB * Epad) s_logit[i] = (t0 + i / Epad < a.T) ? v : 0.f;
+                if (i < TB * EP && e < Epad) s_logit[tr * Epad + e] = (t0 + tr < a.T) ? v : 0.f;
             }
         }
     } else if (a.dtype == ORDERMOE_BF16) {
@@ -594,32 +608,33 @@ route_select_kernel(const RouteArgs a) {
     const int kk1 = (k + 1 < E) ? k + 1 : E;
     // (reads at clamped addresses and selects instead of branches, so that the
     // LDS reads issue together and no per-element branch splits the wave)
+    // Each rank takes the row's largest key with 32-bit maxima, then the lowest
+    // expert that has it (64-bit (logit, expert) keys took 900 cycles a rank, this
+    // about 300); a taken key becomes 0, below every key in play (at least 1).
     uint32_t okey[NBT];
 #pragma unroll
     for (int i = 0; i < NBT; ++i) {
         const int e = j + 16 * i;
-        const float v = lg[e < E ? e : E - 1];
-        okey[i] = e < E ? f2ord(v) : 0u;
+        const uint32_t o = f2ord(lg[e < E ? e : E - 1]);
+        okey[i] = e < E ? (o > 1u ? o : 1u) : 0u;
     }
-    uint32_t removed = 0;                    // bit i: local element j + 16 i taken
     int sel_e[KM + 1];
     float sel_v[KM + 1];
 #pragma unroll
     for (int r = 0; r < KM + 1; ++r) {
         if (r < kk1) {
-            uint64_t best = 0;
+            uint32_t mx = okey[0];
 #pragma unroll
-            for (int i = 0; i < NBT; ++i) {
-                const int e = j + 16 * i;
-                const bool live = e < E && !((removed >> i) & 1u);
-                const uint64_t key = live ? (((uint64_t)okey[i] << 32) | (uint32_t)(0xFFFFu - (uint32_t)e)) : 0ull;
-                best = key > best ? key : best;
-            }
-            best = row_max_u64(best);
-            const int e = (int)(0xFFFFu - (uint32_t)(best & 0xFFFFu));
-            sel_e[r] = e;
-            sel_v[r] = ord2f((uint32_t)(best >> 32));
-            if ((e & 15) == j) removed |= 1u << (e >> 4);
+            for (int i = 1; i < NBT; ++i) mx = okey[i] > mx ? okey[i] : mx;
+            mx = row_max_u32(mx);
+            uint32_t e = 0xFFFFu;
+#pragma unroll
+            for (int i = NBT - 1; i >= 0; --i) e = okey[i] == mx ? (uint32_t)(j + 16 * i) : e;
+            e = row_min_u32(e);
+            sel_e[r] = (int)e;
+            sel_v[r] = ord2f(mx);
+#pragma unroll
+            for (int i = 0; i < NBT; ++i) okey[i] = e == (uint32_t)(j + 16 * i) ? 0u : okey[i];
         }
     }
     float mg = __builtin_inff();
@@ -638,7 +653,8 @@ route_select_kernel(const RouteArgs a) {
             if (r < k) den += expf(sel_v[r] - sel_v[0]);
     } else {
         for (int e = j; e < E; e += 16) den += expf(lg[e] - sel_v[0]);
-        den = row_sum_f32(den);
+        // (the rotations add in another order in every lane: all take lane 0's sum)
+        den = __shfl(row_sum_f32(den), 0, 16);
     }
 
     // server-expert selection.  Lane j holds candidate j of every slot: j = 0
@@ -707,7 +723,11 @@ route_select_kernel(const RouteArgs a) {
             }
         }
     }
-    int first_m = s_loc, ncls[4] = {0, 0, 0, 0}, nremote = 0;
+    // Only the choice is serial over the slots; lane j keeps slot j's, and the
+    // lanes write the token's slots together (lane 0 writing them one after the
+    // other took 5.6 of 19 us at 64 tokens of 128 experts, top-8).
+    int first_m = s_loc, my_r = 0, my_k = 0, my_m = s_loc;
+    float my_v = 0.f;
     uint32_t dstmask = 0;
 #pragma unroll
     for (int slot = 0; slot < KM; ++slot) {
@@ -725,41 +745,39 @@ route_select_kernel(const RouteArgs a) {
             // the chosen candidate's loss, from its lane (a sum of one term: exact)
             qsel = row_sum_f32(j == pos ? qe[slot] : 0.f);
         }
-        const int remote = mm != s_loc;
-        const int c = (remote << 1) | (km != r);
         qhat = qhat + qsel;
         if (slot == 0) first_m = mm;
-        if (valid && j == 0) {
-            const int64_t o = t * k + slot;
-            a.out.idx[o] = r;
-            a.out.w[o] = expf(sel_v[slot] - sel_v[0]) / den;
-            if (loc_ok) {
-                a.out.exec_k[o] = km;
-                a.out.exec_m[o] = (uint8_t)mm;
-                a.out.cls[o] = (uint8_t)c;
-                ncls[c]++;
-                if (remote) { nremote++; dstmask |= 1u << mm; atomicAdd(&s_cnt[8 + mm], 1); }
-            } else {
-                a.out.exec_k[o] = -1;
-                a.out.exec_m[o] = 255;
-                a.out.cls[o] = 255;
-            }
-        }
+        if (mm != s_loc) dstmask |= 1u << mm;
+        if (j == slot) { my_r = r; my_k = km; my_m = mm; my_v = sel_v[slot]; }
     }
+    const bool mine = valid && j < k, placed = mine && loc_ok;
+    const bool remote = my_m != s_loc;
+    const int c = ((int)remote << 1) | (int)(my_k != my_r);
+    if (mine) {
+        const int64_t o = t * k + j;
+        a.out.idx[o] = my_r;
+        a.out.w[o] = expf(my_v - sel_v[0]) / den;
+        a.out.exec_k[o] = loc_ok ? my_k : -1;
+        a.out.exec_m[o] = loc_ok ? (uint8_t)my_m : 255;
+        a.out.cls[o] = loc_ok ? (uint8_t)c : 255;
+        if (loc_ok && remote) atomicAdd(&s_cnt[8 + my_m], 1);
+    }
+    const int fl = mg < ORDERMOE_MARGIN_FLAG;
     if (valid && j == 0) {
         a.out.margin[t] = mg;
-        const int fl = mg < ORDERMOE_MARGIN_FLAG;
         a.out.flag[t] = (uint8_t)fl;
-        a.out.qhat_out[t] = loc_ok ? qhat : a.qhat_in[t];
-        a.out.loc_out[t] = loc_ok ? (uint8_t)first_m : a.loc_in[t];
-        if (loc_ok) {
-            for (int c = 0; c < 4; ++c) if (ncls[c]) atomicAdd(&s_cnt[c], ncls[c]);
-            if (nremote) atomicAdd(&s_cnt[6], nremote);
-            if (dstmask) atomicAdd(&s_cnt[5], __builtin_popcount(dstmask));
-        } else {
-            atomicAdd(&s_cnt[7], 1);
-        }
-        if (fl) atomicAdd(&s_cnt[4], 1);
+        a.out.qhat_out[t] = loc_ok ? qhat : qhat_pre;
+        a.out.loc_out[t] = loc_ok ? (uint8_t)first_m : (uint8_t)loc_pre;
+        if (loc_ok && dstmask) atomicAdd(&s_cnt[5], __builtin_popcount(dstmask));
+    }
+    // the wave's totals: slots by class, flagged tokens, remote slots, tokens off the servers
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (i == 5) continue;
+        const bool hit = i < 4 ? placed && c == i : i == 4 ? valid && j == 0 && fl : i == 6 ? placed && remote
+                                                                                         : valid && j == 0 && !loc_ok;
+        const uint64_t bal = __builtin_amdgcn_ballot_w64(hit);
+        if (lane == 0 && bal) atomicAdd(&s_cnt[i], __popcll(bal));
     }
     }   // token stage
     __syncthreads();
