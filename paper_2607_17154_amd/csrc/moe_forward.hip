@@ -1142,10 +1142,6 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
     const int head = rounds * grid, whole = sp0 - head, ns = items - sp0;
     const TileSeg Ssh = P->seg[p.n_routed];         // the shared group
     for (int r = 0; r <= rounds; ++r) {
-        // lane g reads routed group g's segment (again for every tile: held across the
-        // K loop it would spill), beside the reads of the list's head
-        const int lane = threadIdx.x & 63, n = p.n_routed;
-        const TileSeg V = P->seg[lane < n ? lane : n];
         const int pos = round_pos(vid, r, r < rounds ? grid : whole + split * ns, grid, spread);
         if (pos < 0) break;
         int item = r * grid + pos, lj = 0;
@@ -1154,8 +1150,11 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
             lj = (pos - whole) / ns;                             // K piece of a left-over item
             item = sp0 + (pos - whole) - lj * ns;
         }
-        // the group of the item: the last one that starts at or before it (an empty group
-        // starts where the next one does)
+        // the group of the item: lane g reads routed group g's segment (again for every
+        // tile: held across the K loop it would spill), and the last one that starts at or
+        // before the item is it (an empty group starts where the next one does)
+        const int lane = threadIdx.x & 63, n = p.n_routed;
+        const TileSeg V = P->seg[lane < n ? lane : n];
         const bool shared = item < nsh * q;
         int g = n, mt_hl = Ssh.mt_hl, t = item - Ssh.first;
         TileLoc L;
