@@ -77,3 +77,23 @@ def test_bf16_forward_at_the_tile_edges(rows, d, f, n_shared, here):
     print("rows %s d %d f %d: max err %.3g of the largest output" % (rows[:8], d, f, err), flush=True)
     assert err <= 8 * 2.0 ** -9
     assert ro.cpu().tolist()[:n] == list(np.concatenate([[0], np.cumsum(rows)[:-1]]))
+
+
+@pytest.mark.parametrize("dtype,n,d,f", [("bf16", 1, 256, 128), ("bf16", 3, 768, 640), ("f32", 2, 72, 96),
+                                         ("f32", 1, 512, 32)])
+def test_packed_weights_are_the_documented_layout(dtype, n, d, f):
+    """Every packed element equals the source element that the layout names
+    (K steps that are no multiple of a wave's, one and several experts)."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d * f)
+    wg, wu, wd = (torch.randn(n, *s, generator=g, device="cuda").to(dt) for s in ((f, d), (f, d), (d, f)))
+    gu, dn = torch.full((n, 2 * f, d), 7.0, dtype=dt, device="cuda"), torch.full((n, d, f), 7.0, dtype=dt, device="cuda")
+    om.ordermoe_pack_gate_up(wg, wu, gu)
+    om.ordermoe_pack_down(wd, dn)
+    want = torch.stack([wg.view(n, f // 32, 32, d), wu.view(n, f // 32, 32, d)], 2).reshape(n, 2 * f, d)
+    blk = lambda t, N, K: t.reshape(n, N // 256, 256, K // 64, 64).transpose(2, 3).reshape(n, N, K)  # noqa: E731
+    if dtype == "bf16":
+        assert torch.equal(gu, blk(want, 2 * f, d)) and torch.equal(dn, blk(wd, d, f))
+    else:
+        assert torch.equal(gu, want) and torch.equal(dn, wd)
