@@ -434,8 +434,9 @@ typedef struct {
  * each local expert, then of the shared rows, then the total row count.
  * ws: dev, at least ordermoe_forward_workspace_size(W, T, k) bytes (else
  * ORDERMOE_EWORKSPACE): row tables, the activations, the per-row outputs and,
- * for bf16 batches above 128 tokens, 64 MiB of fp32 partial tiles for GEMM
- * tiles split along K (summed in K order, so results are deterministic).  The
+ * for bf16 batches of more than a few rows per expert, 64 MiB of fp32 partial
+ * tiles for GEMM tiles split along K (summed in K order, so results are
+ * deterministic) and the GEMMs' work lists.  The
  * call uses it until the stream passes the call; calls in flight at the same
  * time need workspaces of their own. */
 size_t ordermoe_forward_workspace_size(const ordermoe_experts* W, int64_t T, int32_t k);

@@ -107,10 +107,9 @@ struct ForwardArgs {
 };
 int launch_local_forward(const ForwardArgs& a, void* stream);
 int forward_tokens_per_block();
-bool forward_uses_thin(int dtype, int64_t T);
-void forward_tile_shape(int dtype, int64_t T, int* bm_gu, int* bn_gu, int* bm_dn, int* bn_dn);
+bool forward_uses_thin(int dtype, int64_t T, int k, int E, int n_shared);
 size_t forward_split_counters();
-size_t forward_split_floats(int dtype, int64_t T);
+size_t forward_split_floats(int dtype, bool thin);
 
 struct SimArgs {
     int dtype, d, E, k;

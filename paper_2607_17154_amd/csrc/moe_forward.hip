@@ -21,7 +21,7 @@
 // (row counts are never read by the host).  Tiles of one expert are ordered
 // m-fastest so consecutive tiles share a weight tile, and workgroup ids are
 // remapped so that each XCD (and its L2) works on a contiguous range of tiles.
-// The bf16 GEMMs of more than 128 tokens fit the tile heights to the row counts
+// The tiled bf16 GEMMs fit the tile heights to the row counts
 // (64 to 256 rows, see TilePlan): whole rounds of tiles, one tile per workgroup
 // per round, then the tiles left over, cut along K into pieces at the same
 // positions in every tile where that ends the launch sooner; the last workgroup
@@ -1598,9 +1598,16 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 }
 
 
-// bf16 batches of at most THIN_MAX_T tokens (every expert then has at most that
-// many rows) take the thin GEMM, THIN_PER_CU resident workgroups per CU
-constexpr int64_t THIN_MAX_T = 128;
+// bf16 batches that take the thin GEMM, THIN_PER_CU resident workgroups per CU:
+// few rows per expert by the batch's mean (T k / E; the rows are not known here),
+// where the weight stream is all there is.  Thin against tiled, us per layer: 128
+// experts of d = 4096 top-8, 140 tokens 226 and 249, 256 tokens 239 and 254;
+// 8 experts of d = 4096, f = 14336 top-2, 64 tokens 150 and 151, 128 tokens (35 rows
+// per expert, a second row tile) 201 and 154.  Two or more shared experts form one
+// group with several times the routed K, which the thin GEMM runs whole and the
+// tiled one in K pieces: 4 shared, 64 tokens 89 and 86, 128 tokens 106 and 93.
+constexpr int64_t THIN_MAX_T = 512, THIN_SHARED_T = 32;
+constexpr int THIN_ROWS = 20;
 // Routed gate/up weights of at least this many bytes are streamed by short single
 // row tiles with non-temporal loads: 805 MB (32 experts of d = 4096, f = 1536)
 // 148 -> 131 us, 92 MB (8 of d = 2048, f = 1408) 53 -> 49 us; smaller ones are
@@ -1633,29 +1640,28 @@ int bf16_grid(int64_t upper_tiles) {
 
 size_t forward_split_counters() { return 2 * SK_MAX_GRID; }
 
-size_t forward_split_floats(int dtype, int64_t T) {
-    if (dtype != ORDERMOE_BF16 || forward_uses_thin(dtype, T)) return 0;
+size_t forward_split_floats(int dtype, bool thin) {
+    if (dtype != ORDERMOE_BF16 || thin) return 0;
     static_assert(2 * sizeof(TilePlan) <= 256 * TP_BN * sizeof(float), "the work lists fit the last slot");
     return (size_t)SK_MAX_GRID * 256 * TP_BN;
 }
 
 int forward_tokens_per_block() { return FT_TB; }
 
-bool forward_uses_thin(int dtype, int64_t T) { return dtype == ORDERMOE_BF16 && T <= THIN_MAX_T; }
-
-void forward_tile_shape(int dtype, int64_t T, int* bm_gu, int* bn_gu, int* bm_dn, int* bn_dn) {
-    if (forward_uses_thin(dtype, T)) { *bm_gu = *bm_dn = TH_BM; *bn_gu = *bn_dn = TH_BN; }
-    else if (dtype == ORDERMOE_BF16) { *bm_gu = *bm_dn = 64; *bn_gu = *bn_dn = TP_BN; }   // (the shortest tile)
-    else { *bm_gu = F32_BM; *bn_gu = F32_BN; *bm_dn = F32_BM; *bn_dn = F32_BN; }
+bool forward_uses_thin(int dtype, int64_t T, int k, int E, int n_shared) {
+    if (dtype != ORDERMOE_BF16) return false;
+    return n_shared >= 2 ? T <= THIN_SHARED_T : T <= THIN_MAX_T && T * k <= (int64_t)THIN_ROWS * E;
 }
 
 int launch_local_forward(const ForwardArgs& f, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     const int has_sh = f.n_shared > 0 ? 1 : 0;
     const int G = f.n_local + has_sh;
-    const bool thin = forward_uses_thin(f.dtype, f.T);
-    int bm_gu, bn_gu, bm_dn, bn_dn;
-    forward_tile_shape(f.dtype, f.T, &bm_gu, &bn_gu, &bm_dn, &bn_dn);
+    const bool thin = forward_uses_thin(f.dtype, f.T, f.k, f.E, f.n_shared);
+    // tile geometry (of the tiled bf16 GEMMs the shortest tile, for the grids)
+    const bool bf = f.dtype == ORDERMOE_BF16;
+    const int bm_gu = thin ? TH_BM : bf ? 64 : F32_BM, bm_dn = bm_gu;
+    const int bn_gu = thin ? TH_BN : bf ? TP_BN : F32_BN, bn_dn = bn_gu;
     const int64_t rows_r = f.rmax_routed, rows_s = has_sh ? f.T : 0;
     // upper bounds of the tiles, for the grids
     const int64_t ub_gu = ((rows_r + bm_gu - 1) / bm_gu + f.n_local) * (2 * f.f / bn_gu) +
