@@ -1010,8 +1010,13 @@ __device__ __attribute__((always_inline)) inline void bf16_tile(const GemmArgs& 
         step(I0{}, kt); step(I1{}, kt);
         if (kt + 2 < kt_hi) { step(I2{}, kt); step(I3{}, kt); }
     }
-    // loads of the tiles after the last may still be in flight
+    // loads of the tiles after the last may still be in flight: this wave waits
+    // for its own, and the barrier holds until every wave's have arrived.  Which
+    // rows a wave loads depends on the tile height, so without it a late wave's
+    // loads could overwrite rows that another wave loads for the next tile; the
+    // epilogues also reuse sB2.
     __builtin_amdgcn_s_waitcnt(0x0F70);
+    lds_barrier();
 
     if (nseg > 1) {
         // a piece of a split tile: its partial sums go to slot j sstride + ctr
@@ -1082,11 +1087,9 @@ __device__ __attribute__((always_inline)) inline void bf16_tile(const GemmArgs& 
 
     // epilogue: element e of a 32x32 block is row (e/4)*8 + (lane_r/32)*4 + e%4,
     // column lane_r%32.  Down scales each row by its gate weight, parked in
-    // LDS by the workgroup (the barrier also orders it after the previous
-    // tile's reads, which precede this tile's K-loop barriers).
+    // LDS by the workgroup (in sB2, idle since the barrier after the K loop; the
+    // previous tile's reads precede this tile's K-loop barriers).
     if constexpr (MODE == 1) {
-        // (in sB2: after every wave's last fragment reads of the K loop)
-        lds_barrier();
         if (tid_r < BM) s_roww[tid_r] = roww;
         lds_barrier();
     }
