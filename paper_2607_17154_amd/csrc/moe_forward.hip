@@ -737,7 +737,8 @@ constexpr int waitcnt_enc(int vm, int lgkm) { return (vm & 0xF) | ((vm >> 4) << 
 // memory accesses across it.  The caller first waits (s_waitcnt vmcnt) for its
 // own loads into the buffers read after the barrier, and every LDS read of a
 // buffer has returned its data (it fed an MFMA) before the barrier that
-// precedes the next load into that buffer.
+// precedes the next load into that buffer.  Nothing waits for LDS writes
+// either: __syncthreads() where other waves read them.
 __device__ inline void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -1091,7 +1092,7 @@ __device__ __attribute__((always_inline)) inline void bf16_tile(const GemmArgs& 
     // previous tile's reads precede this tile's K-loop barriers).
     if constexpr (MODE == 1) {
         if (tid_r < BM) s_roww[tid_r] = roww;
-        lds_barrier();
+        __syncthreads();     // (waits for the write, which the bare barrier does not; no load is in flight)
     }
     const int rbase = L.m0 + wm_r * WM + (lane_r >> 5) * 4;
     if constexpr (MODE == 0) {

@@ -77,3 +77,20 @@ def test_a_tile_loads_after_every_wave_has_drained_the_last_one(kernels, name):
     lines = next(v for k, v in kernels.items() if name in k)
     assert any(map(_is_lds_load, lines)) and "s_barrier" in lines
     assert _violations(lines, _tile_change) == []
+
+
+def _lds_write(s, state):
+    """state 1: a write to LDS may be outstanding; a barrier then lets other waves read the old value."""
+    if s.startswith("ds_write"):
+        return 1, False
+    if _waits(s, "lgkmcnt"):
+        return 0, False
+    return state, state == 1 and s == "s_barrier"
+
+
+@pytest.mark.parametrize("name", ["ggemm_bf16ILi0E", "ggemm_bf16ILi1E", "ggemm_f32ILi0E", "ggemm_f32ILi1E",
+                                  "ggemm_thinILi0E", "ggemm_thinILi1E"])
+def test_lds_writes_are_done_before_a_barrier(kernels, name):
+    lines = next(v for k, v in kernels.items() if name in k)
+    assert any(s.startswith("ds_write") for s in lines) and "s_barrier" in lines
+    assert _violations(lines, _lds_write) == []
