@@ -642,7 +642,7 @@ struct GemmArgs {
     void* Os;                 // mode 0: shared activations out; mode 1: unused
     const float* row_w;       // mode 1
     const TilePlan* plan;     // bf16 tiled: the work list
-    int stream;               // bf16 tiled gate/up: see STREAM_BYTES
+    int stream;               // bf16: see STREAM_BYTES
     float* sk_part;           // bf16 tiled: [sk_slots(H)][64 H * 256] partial tiles of split tiles
     int32_t* sk_cnt;          // bf16: [2][SK_MAX_GRID] arrival counters (zero at launch)
 };
@@ -1237,12 +1237,12 @@ __global__ void __launch_bounds__(256, 1) ggemm_bf16(const GemmArgs p) {
 // memory straight into MFMA registers.  Two register sets keep the next step's
 // reads in flight during the current step.  The waves' partial sums meet in LDS
 // and are added in wave order, then the epilogue of ggemm_bf16 runs on the
-// sums.  The weights of an expert of at most 32 rows are read exactly once, as
-// non-temporal loads: those stream at 7.0 TB/s here, ordinary ones at 6.2 (64
-// tokens, 30 experts of d = 4096, f = 1536: layer 245 -> 225 us; one token 58 ->
-// 55 us).  With more row tiles the tiles after the first find the weights in
-// L2, which non-temporal loads would forfeit (2 x 35 rows of d = 4096,
-// f = 14336: 205 -> 231 us), so those keep ordinary loads.
+// sums.  The weights of an expert of at most 32 rows are read exactly once, in a
+// layer of STREAM_BYTES or more with non-temporal loads: those stream at 7.0 TB/s
+// here, ordinary ones at 6.2 (64 tokens, 30 experts of d = 4096, f = 1536: layer
+// 245 -> 225 us; one token 58 -> 55 us).  With more row tiles the tiles after the
+// first find the weights in L2, which non-temporal loads would forfeit (2 x 35 rows
+// of d = 4096, f = 14336: 205 -> 231 us), so those keep ordinary loads.
 constexpr int TH_BM = 32, TH_BN = 64, TH_WAVES = 4;
 constexpr int TH_LDK = 144;                        // bytes per staged weight row
 constexpr int TH_LDS = TH_WAVES * TH_BN * TH_LDK;  // staging; reused for the partial sums
@@ -1303,8 +1303,9 @@ ggemm_thin(const GemmArgs p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) { acc0[e] = 0.f; acc1[e] = 0.f; }
         bf16x8 w[2][8], a[2][4];
-        // weights that one row tile reads are read once: non-temporal
-        const bool once = L.R <= TH_BM;
+        // weights that one row tile reads are read once: non-temporal where the
+        // layer outgrows the caches
+        const bool once = p.stream && L.R <= TH_BM;
         auto load = [&](auto nt, int buf, int it) {
             constexpr int AUX = decltype(nt)::value;
             const int st = wave + it * TH_WAVES;
@@ -1612,11 +1613,14 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 // tiled one in K pieces: 4 shared, 64 tokens 89 and 86, 128 tokens 106 and 93.
 constexpr int64_t THIN_MAX_T = 512, THIN_SHARED_T = 32;
 constexpr int THIN_ROWS = 20;
-// Routed gate/up weights of at least this many bytes are streamed by short single
-// row tiles with non-temporal loads: 805 MB (32 experts of d = 4096, f = 1536)
-// 148 -> 131 us, 92 MB (8 of d = 2048, f = 1408) 53 -> 49 us; smaller ones are
-// found in the caches by the next call, which such loads forfeit: 21 MB (8 of
-// d = 1024, f = 640) 15 -> 19 us.  (In the down GEMM the further tile variants
+// Routed gate/up weights of at least this many bytes are streamed with non-temporal
+// loads by short single row tiles and by the thin GEMM.  Tiled gate/up: 805 MB (32
+// experts of d = 4096, f = 1536) 148 -> 131 us, 92 MB (8 of d = 2048, f = 1408)
+// 53 -> 49 us; smaller ones are found in the caches by the next call, which such
+// loads forfeit: 21 MB (8 of d = 1024, f = 640) 15 -> 19 us.  Thin, the whole layer
+// at 4 and 64 tokens: over three layers in turn 92 MB and 173 MB (15 of d = 2048,
+// f = 1408) 2 to 5% faster, 21 MB 5 to 8% slower; over one layer of 92 MB again and
+// again, which then stays in the caches, 6% slower.  (In the down GEMM the further tile variants
 // spilled: 78 -> 85 us at the first shape; it keeps ordinary loads.)
 constexpr int64_t STREAM_BYTES = 64 << 20;
 constexpr int THIN_PER_CU = 3;
@@ -1721,6 +1725,7 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     g.X = f.x; g.row_tok = f.row_tok; g.ldx = f.d; g.row_w = f.row_w;
     g.x_bytes = (uint32_t)((size_t)f.T * f.d * (f.dtype == ORDERMOE_BF16 ? 2 : 4));
     g.sk_part = f.sk_part; g.sk_cnt = f.sk_cnt;
+    g.stream = (int64_t)f.n_local * 2 * f.f * f.d * 2 >= STREAM_BYTES;
 
     // gate/up: [rows][d] x [2f][d]^T -> activations [rows][f]
     g.ntiles = f.tile_info + 0;
@@ -1736,7 +1741,6 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
         {
         KernelTimer kt_("gemm_gate_up", st);
         g.plan = plan;
-        g.stream = (int64_t)f.n_local * 2 * f.f * f.d * 2 >= STREAM_BYTES;
         ggemm_bf16<0><<<dim3(r.shape[0].grid), dim3(256), 0, st>>>(g);
         }
         if ((e = hipGetLastError()) != hipSuccess) return (int)e;
