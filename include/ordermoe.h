@@ -434,9 +434,10 @@ typedef struct {
  * each local expert, then of the shared rows, then the total row count.
  * ws: dev, at least ordermoe_forward_workspace_size(W, T, k) bytes (else
  * ORDERMOE_EWORKSPACE): row tables, the activations, the per-row outputs and,
- * for bf16 batches of more than a few rows per expert, 64 MiB of fp32 partial
- * tiles for GEMM tiles split along K (summed in K order, so results are
- * deterministic) and the GEMMs' work lists.  The
+ * for bf16 batches that take the tiled GEMMs, 64 MiB of fp32 partial tiles for
+ * GEMM tiles split along K (summed in K order, so results are deterministic) and
+ * the GEMMs' work lists: T > 128, unless T <= 512, n_shared < 2 and T k <= 20 E;
+ * T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E.  The
  * call uses it until the stream passes the call; calls in flight at the same
  * time need workspaces of their own. */
 size_t ordermoe_forward_workspace_size(const ordermoe_experts* W, int64_t T, int32_t k);

@@ -107,7 +107,7 @@ struct ForwardArgs {
 };
 int launch_local_forward(const ForwardArgs& a, void* stream);
 int forward_tokens_per_block();
-bool forward_uses_thin(int dtype, int64_t T, int k, int E, int n_shared);
+bool forward_uses_thin(int dtype, int64_t T, int k, int E, int f, int n_shared);
 size_t forward_split_counters();
 size_t forward_split_floats(int dtype, bool thin);
 

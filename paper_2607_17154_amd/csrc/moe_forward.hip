@@ -1603,16 +1603,20 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 }
 
 
-// bf16 batches that take the thin GEMM, THIN_PER_CU resident workgroups per CU:
-// few rows per expert by the batch's mean (T k / E; the rows are not known here),
-// where the weight stream is all there is.  Thin against tiled, us per layer: 128
-// experts of d = 4096 top-8, 140 tokens 226 and 249, 256 tokens 239 and 254;
-// 8 experts of d = 4096, f = 14336 top-2, 64 tokens 150 and 151, 128 tokens (35 rows
-// per expert, a second row tile) 201 and 154.  Two or more shared experts form one
-// group with several times the routed K, which the thin GEMM runs whole and the
-// tiled one in K pieces: 4 shared, 64 tokens 89 and 86, 128 tokens 106 and 93.
-constexpr int64_t THIN_MAX_T = 512, THIN_SHARED_T = 32;
-constexpr int THIN_ROWS = 20;
+// bf16 batches that take the thin GEMM, THIN_PER_CU resident workgroups per CU.
+// Up to THIN_MAX_T tokens it is the safe choice whatever rows the experts get: the
+// tiled one takes half as long again when the local experts get few rows (15
+// experts of d = 2048, f = 1408, one row: 24 us thin, 36 tiled), the thin one at
+// most twice as long when a few experts get all tokens.  Except where THIN_ROWS rows
+// per expert are the mean and one expert's gate/up tiles fill half the chip
+// (f >= TILED_F): 2 experts of f = 14336, 128 tokens, 1, 2 x 2 and 2 x 32 rows: thin
+// 82, 124 and 157 us, tiled 85, 119 and 123; f = 12288: tiled at most the time that
+// thin takes, f = 7168: 79 against 68 with few rows.
+// Above, up to THIN_SPARSE_T tokens, a mean of at most THIN_ROWS rows per expert: 128
+// experts of d = 4096 top-8, 140 tokens 226 us thin and 249 tiled, 256 tokens 239
+// and 254.
+constexpr int64_t THIN_MAX_T = 128, THIN_SPARSE_T = 512;
+constexpr int THIN_ROWS = 20, TILED_F = 12288;
 // Routed gate/up weights of at least this many bytes are streamed with non-temporal
 // loads by short single row tiles and by the thin GEMM.  Tiled gate/up: 805 MB (32
 // experts of d = 4096, f = 1536) 148 -> 131 us, 92 MB (8 of d = 2048, f = 1408)
@@ -1656,16 +1660,17 @@ size_t forward_split_floats(int dtype, bool thin) {
 
 int forward_tokens_per_block() { return FT_TB; }
 
-bool forward_uses_thin(int dtype, int64_t T, int k, int E, int n_shared) {
+bool forward_uses_thin(int dtype, int64_t T, int k, int E, int f, int n_shared) {
     if (dtype != ORDERMOE_BF16) return false;
-    return n_shared >= 2 ? T <= THIN_SHARED_T : T <= THIN_MAX_T && T * k <= (int64_t)THIN_ROWS * E;
+    const bool few = T * k <= (int64_t)THIN_ROWS * E;
+    return T <= THIN_MAX_T ? few || f < TILED_F || n_shared >= 2 : few && T <= THIN_SPARSE_T && n_shared < 2;
 }
 
 int launch_local_forward(const ForwardArgs& f, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     const int has_sh = f.n_shared > 0 ? 1 : 0;
     const int G = f.n_local + has_sh;
-    const bool thin = forward_uses_thin(f.dtype, f.T, f.k, f.E, f.n_shared);
+    const bool thin = forward_uses_thin(f.dtype, f.T, f.k, f.E, f.f, f.n_shared);
     // tile geometry (of the tiled bf16 GEMMs the shortest tile, for the grids)
     const bool bf = f.dtype == ORDERMOE_BF16;
     const int bm_gu = thin ? TH_BM : bf ? 64 : F32_BM, bm_dn = bm_gu;

@@ -271,6 +271,27 @@ def test_workspace_sizes_are_monotone():
     assert 0 < s1 < s2
 
 
+PARTIAL_TILES = 64 << 20       # workspace of the tiled bf16 GEMMs
+
+
+@pytest.mark.parametrize("d,f,E,k,n_shared", [
+    (2048, 1408, 60, 4, 4), (2048, 1408, 64, 6, 2),    # shared experts side by side: a K several times the routed one
+    (512, 1024, 8, 2, 0), (4096, 7168, 8, 2, 0),       # many rows per expert by the mean, few column tiles
+    (4096, 1536, 128, 8, 0),
+])
+def test_batches_of_128_tokens_need_no_partial_tiles(d, f, E, k, n_shared):
+    """They take the thin GEMM, which no distribution of the rows makes much
+    slower, and which needs no partial tiles."""
+    ids = np.array([0, 4], np.int32)
+    ex = om.Experts(dtype=om.BF16, d=d, f=f, E=E, n_local=2, n_shared=n_shared)
+    ex.local_experts = ids.ctypes.data_as(ctypes.c_void_p)
+    ex.w_gate_up = ex.w_down = ex.w_shared_gate_up = ex.w_shared_down = 16
+    size = lambda T: om.ordermoe_forward_workspace_size(ex, T, k)  # noqa: E731
+    for T in (1, 33, 97, 128):
+        assert 0 < size(T) < PARTIAL_TILES
+    assert size(513) > PARTIAL_TILES
+
+
 def test_forward_rejects_operands_past_31_bit_offsets():
     """The GEMMs address operands with 32-bit byte offsets: T*d*esz, 2*f*d*esz,
     2*n_shared*f*d*esz and T*n_shared*f*esz must stay below 2^31 (no launch)."""
