@@ -437,7 +437,8 @@ typedef struct {
  * for bf16 batches that take the tiled GEMMs, 64 MiB of fp32 partial tiles for
  * GEMM tiles split along K (summed in K order, so results are deterministic) and
  * the GEMMs' work lists: T > 128, unless T <= 512, n_shared < 2 and T k <= 20 E;
- * T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E.  The
+ * T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E (a workspace smaller by
+ * the 64 MiB is accepted there and the batch takes the untiled GEMMs).  The
  * call uses it until the stream passes the call; calls in flight at the same
  * time need workspaces of their own. */
 size_t ordermoe_forward_workspace_size(const ordermoe_experts* W, int64_t T, int32_t k);

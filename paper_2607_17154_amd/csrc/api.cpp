@@ -241,7 +241,11 @@ static int64_t fwd_rmax_routed(const ordermoe_experts* W, int64_t T, int32_t k) 
     return T * (int64_t)std::min(k, W->n_local);
 }
 
-static size_t fwd_ws(const ordermoe_experts* W, int64_t T, int32_t k, Carver& c, ForwardArgs* a) {
+static int fwd_gemms(const ordermoe_experts* W, int64_t T, int32_t k, bool room) {
+    return forward_gemms(W->dtype, T, k, W->E, W->f, W->n_shared, room);
+}
+
+static size_t fwd_ws(const ordermoe_experts* W, int64_t T, int32_t k, int gemms, Carver& c, ForwardArgs* a) {
     const int tb = forward_tokens_per_block();
     const int nblk = (int)((T + tb - 1) / tb);
     const int has_sh = W->n_shared > 0;
@@ -258,12 +262,12 @@ static size_t fwd_ws(const ordermoe_experts* W, int64_t T, int32_t k, Carver& c,
     char* as = c.take<char>((size_t)rs * W->n_shared * W->f * esz);
     char* ob = c.take<char>((size_t)(rr + rs) * W->d * esz);
     int32_t* sc = c.take<int32_t>(forward_split_counters());
-    float* sp = c.take<float>(forward_split_floats(W->dtype, forward_uses_thin(W->dtype, T, k, W->E, W->f, W->n_shared)));
+    float* sp = c.take<float>(forward_split_floats(gemms));
     if (a) {
         a->blk_rows = br; a->row_tok = rt; a->row_w = rw; a->tok_rows = tr;
         a->tile_info = ti; a->act_r = ar; a->act_s = as; a->obuf = ob; a->rmax_routed = rr;
         a->sk_cnt = sc; a->sk_part = sp;
-        a->nblk = nblk;
+        a->nblk = nblk; a->gemms = gemms;
     }
     return c.size();
 }
@@ -316,7 +320,7 @@ extern "C" size_t ordermoe_forward_workspace_size(const ordermoe_experts* W, int
     if (check_experts(W) != ORDERMOE_OK || T < 0 || k < 1 || k > ORDERMOE_MAX_TOPK) return 0;
     if (!operands_fit_31_bits(W, T)) return 0;
     Carver c(nullptr);
-    return fwd_ws(W, T, k, c, nullptr);
+    return fwd_ws(W, T, k, fwd_gemms(W, T, k, true), c, nullptr);
 }
 
 extern "C" int ordermoe_local_moe_forward(const ordermoe_experts* W, const void* x, int64_t T,
@@ -338,7 +342,11 @@ extern "C" int ordermoe_local_moe_forward(const ordermoe_experts* W, const void*
         return fail(ORDERMOE_EINVAL, "local_moe_forward: null pointer");
     if (T > 0 && (!aligned16(x) || !aligned16(y)))
         return fail(ORDERMOE_EINVAL, "local_moe_forward: x and y must be 16-byte aligned");
-    const size_t need = ordermoe_forward_workspace_size(W, T, k);
+    // a workspace without room for partial tiles is enough where the thin GEMMs can take the batch
+    int gemms = fwd_gemms(W, T, k, true);
+    auto size = [&] { Carver m(nullptr); return fwd_ws(W, T, k, gemms, m, nullptr); };
+    if (ws_bytes < size()) gemms = fwd_gemms(W, T, k, false);
+    const size_t need = size();
     if (!ws || ws_bytes < need)
         return fail(ORDERMOE_EWORKSPACE, "local_moe_forward: workspace needs " + std::to_string(need) + " bytes");
 
@@ -352,7 +360,7 @@ extern "C" int ordermoe_local_moe_forward(const ordermoe_experts* W, const void*
     a.x = x; a.T = T; a.w = w; a.exec_k = exec_k; a.exec_m = exec_m; a.loc_in = loc_in;
     a.server = server; a.y = y; a.row_offsets = row_offsets;
     Carver c(ws);
-    fwd_ws(W, T, k, c, &a);
+    fwd_ws(W, T, k, gemms, c, &a);
     const int e = launch_local_forward(a, stream);
     if (e) return hip_fail(e, "local_moe_forward launch");
     clear_error();

@@ -104,12 +104,15 @@ struct ForwardArgs {
     int32_t* sk_cnt;       // [forward_split_counters()] arrival counters of split tiles
     int64_t rmax_routed;
     int nblk;
+    int gemms;             // forward_gemms
 };
 int launch_local_forward(const ForwardArgs& a, void* stream);
 int forward_tokens_per_block();
-bool forward_uses_thin(int dtype, int64_t T, int k, int E, int f, int n_shared);
+// the GEMMs that a bf16 batch takes (0 for fp32); room: the workspace holds the tiled ones' partial tiles
+constexpr int GEMM_THIN = 1, GEMM_TILED = 2;
+int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, bool room);
 size_t forward_split_counters();
-size_t forward_split_floats(int dtype, bool thin);
+size_t forward_split_floats(int gemms);
 
 struct SimArgs {
     int dtype, d, E, k;

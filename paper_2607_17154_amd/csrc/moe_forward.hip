@@ -1652,25 +1652,26 @@ int bf16_grid(int64_t upper_tiles) {
 
 size_t forward_split_counters() { return 2 * SK_MAX_GRID; }
 
-size_t forward_split_floats(int dtype, bool thin) {
-    if (dtype != ORDERMOE_BF16 || thin) return 0;
+size_t forward_split_floats(int gemms) {
+    if (!(gemms & GEMM_TILED)) return 0;
     static_assert(2 * sizeof(TilePlan) <= 256 * TP_BN * sizeof(float), "the work lists fit the last slot");
     return (size_t)SK_MAX_GRID * 256 * TP_BN;
 }
 
 int forward_tokens_per_block() { return FT_TB; }
 
-bool forward_uses_thin(int dtype, int64_t T, int k, int E, int f, int n_shared) {
-    if (dtype != ORDERMOE_BF16) return false;
+int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, bool room) {
+    if (dtype != ORDERMOE_BF16) return 0;
     const bool few = T * k <= (int64_t)THIN_ROWS * E;
-    return T <= THIN_MAX_T ? few || f < TILED_F || n_shared >= 2 : few && T <= THIN_SPARSE_T && n_shared < 2;
+    if (T <= THIN_MAX_T) return few || f < TILED_F || n_shared >= 2 || !room ? GEMM_THIN : GEMM_TILED;
+    return few && T <= THIN_SPARSE_T && n_shared < 2 ? GEMM_THIN : GEMM_TILED;
 }
 
 int launch_local_forward(const ForwardArgs& f, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     const int has_sh = f.n_shared > 0 ? 1 : 0;
     const int G = f.n_local + has_sh;
-    const bool thin = forward_uses_thin(f.dtype, f.T, f.k, f.E, f.f, f.n_shared);
+    const bool thin = f.gemms & GEMM_THIN;
     // tile geometry (of the tiled bf16 GEMMs the shortest tile, for the grids)
     const bool bf = f.dtype == ORDERMOE_BF16;
     const int bm_gu = thin ? TH_BM : bf ? 64 : F32_BM, bm_dn = bm_gu;
@@ -1680,7 +1681,7 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     const int64_t ub_gu = ((rows_r + bm_gu - 1) / bm_gu + f.n_local) * (2 * f.f / bn_gu) +
                           (has_sh ? ((rows_s + bm_gu - 1) / bm_gu + 1) * (2 * f.n_shared * f.f / bn_gu) : 0);
     const int64_t ub_dn = ((rows_r + rows_s + bm_dn - 1) / bm_dn + G) * (f.d / bn_dn);
-    const bool tiled = !thin && f.dtype == ORDERMOE_BF16;
+    const bool tiled = f.gemms & GEMM_TILED;
     TilePlan* plan = tiled ? (TilePlan*)(f.sk_part + (size_t)(SK_MAX_GRID - 1) * 256 * TP_BN) : nullptr;
 
     RowsArgs r;

@@ -79,6 +79,35 @@ def test_bf16_forward_at_the_tile_edges(rows, d, f, n_shared, here):
     assert ro.cpu().tolist()[:n] == list(np.concatenate([[0], np.cumsum(rows)[:-1]]))
 
 
+def test_a_workspace_without_partial_tiles_is_enough_for_a_decode_batch():
+    """128 tokens of wide experts take the tiled GEMMs, and the thin ones in a
+    workspace that only they fit.  The two add in another order: the bound is the
+    three bf16 roundings' (above)."""
+    n, E, T, k, d, f = 2, 8, 128, 2, 256, 12288
+    bf = torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    mk = lambda *s: (torch.randn(*s, generator=g, device="cuda") * s[-1] ** -0.5).to(bf)  # noqa: E731
+    gu, dn, x = mk(n, 2 * f, d), mk(n, d, f), torch.randn(T, d, generator=g, device="cuda").to(bf)
+    w = torch.rand(T, k, generator=g, device="cuda")
+    ek = torch.arange(k, dtype=torch.int32, device="cuda").repeat(T, 1)
+    m = torch.zeros((T, k), dtype=torch.uint8, device="cuda")
+    loc = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    ex = om.make_experts(om.BF16, d, f, E, list(range(n)), gu, dn, 0, None, None)
+    need = om.ordermoe_forward_workspace_size(ex, T, k)
+    ys = []
+    for size in (need, need - (64 << 20)):
+        y, ro = torch.empty((T, d), dtype=bf, device="cuda"), torch.empty(n + 2, dtype=torch.int32, device="cuda")
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        om.ordermoe_local_moe_forward(ex, x, T, k, w, ek, m, loc, 0, y, ro, ws)
+        torch.cuda.synchronize()
+        ys.append(y.double())
+    assert (ys[0] - ys[1]).abs().amax() <= 8 * 2.0 ** -9 * ys[0].abs().amax()
+    with pytest.raises(om.OrderMoEError) as ei:
+        om.ordermoe_local_moe_forward(ex, x, T, k, w, ek, m, loc, 0, y, ro, ws[:-1])
+    assert ei.value.code == om.EWORKSPACE
+
+
 @pytest.mark.parametrize("dtype,n,d,f", [("bf16", 1, 256, 128), ("bf16", 3, 768, 640), ("f32", 2, 72, 96),
                                          ("f32", 1, 512, 32)])
 def test_packed_weights_are_the_documented_layout(dtype, n, d, f):
