@@ -436,9 +436,11 @@ typedef struct {
  * ORDERMOE_EWORKSPACE): row tables, the activations, the per-row outputs and,
  * for bf16 batches that take the tiled GEMMs, 64 MiB of fp32 partial tiles for
  * GEMM tiles split along K (summed in K order, so results are deterministic) and
- * the GEMMs' work lists: T > 128, unless T <= 512, n_shared < 2 and T k <= 20 E;
- * T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E (a workspace smaller by
- * the 64 MiB is accepted there and the batch takes the untiled GEMMs).  The
+ * the GEMMs' work lists: T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E,
+ * and T > 128, except T <= 160 where n_shared < 2, T k <= 20 E and the routed
+ * gate/up weights take less than 64 MiB.  (A workspace smaller by the 64 MiB is accepted, and the batch takes
+ * the untiled GEMMs, where T <= 128, and where T <= 512, n_shared < 2 and
+ * T k <= 20 E.)  The
  * call uses it until the stream passes the call; calls in flight at the same
  * time need workspaces of their own. */
 size_t ordermoe_forward_workspace_size(const ordermoe_experts* W, int64_t T, int32_t k);

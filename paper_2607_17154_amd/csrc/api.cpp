@@ -242,7 +242,7 @@ static int64_t fwd_rmax_routed(const ordermoe_experts* W, int64_t T, int32_t k) 
 }
 
 static int fwd_gemms(const ordermoe_experts* W, int64_t T, int32_t k, bool room) {
-    return forward_gemms(W->dtype, T, k, W->E, W->f, W->n_shared, room);
+    return forward_gemms(W->dtype, T, k, W->E, W->f, W->n_shared, (int64_t)W->n_local * 2 * W->f * W->d * 2, room);
 }
 
 static size_t fwd_ws(const ordermoe_experts* W, int64_t T, int32_t k, int gemms, Carver& c, ForwardArgs* a) {

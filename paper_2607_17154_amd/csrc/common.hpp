@@ -108,9 +108,10 @@ struct ForwardArgs {
 };
 int launch_local_forward(const ForwardArgs& a, void* stream);
 int forward_tokens_per_block();
-// the GEMMs that a bf16 batch takes (0 for fp32); room: the workspace holds the tiled ones' partial tiles
+// the GEMMs that a bf16 batch takes (0 for fp32), of gu_bytes of routed gate/up weights; room: the workspace holds
+// the tiled ones' partial tiles
 constexpr int GEMM_THIN = 1, GEMM_TILED = 2;
-int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, bool room);
+int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, int64_t gu_bytes, bool room);
 size_t forward_split_counters();
 size_t forward_split_floats(int gemms);
 

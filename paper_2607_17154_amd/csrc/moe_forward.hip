@@ -118,6 +118,7 @@ struct RowsArgs {
     // bf16 tiled GEMMs: work lists of gate/up and down, published by the row kernels (null otherwise)
     TilePlan* plan;           // [2]
     PlanShape shape[2];
+    int choose;               // bf16: thin or tiled GEMMs by the row counts (both are launched, one finds no tiles)
 };
 
 // One token's slots as read from memory: executing server, expert and gate
@@ -267,10 +268,16 @@ constexpr int SCAN_WAVES = SCAN_THREADS / 64;
 
 // One wave: the group offsets (exclusive scan of the group totals tot[0..G),
 // local experts then the shared group) into first[], and, when `publish`, the
-// row offsets and the tile counts of the two GEMMs into device memory.
-__device__ inline void group_layout(const RowsArgs& a, const int32_t* tot, int32_t* first, int lane, bool publish) {
+// row offsets and the tile counts of the two GEMMs into device memory.  Returns
+// whether the tiled GEMMs have work (bf16).  Where the row counts choose (a.choose;
+// all groups have the same shape), the thin GEMM takes the batch unless its row
+// tiles outnumber the groups in use by more than a quarter: 32 of 128 experts of
+// d = 4096, f = 1536, thin and tiled us: 320 tokens, 20 rows each 200 and 222; one of
+// 320, 31 of 10 rows (1.28) 230 and 233; 16 of 160 rows (5) 352 and 167; 512 tokens,
+// 8 of 512 rows 507 and 177.
+__device__ inline bool group_layout(const RowsArgs& a, const int32_t* tot, int32_t* first, int lane, bool publish) {
     const int G = a.n_local + a.has_shared;
-    int32_t base = 0, tiles_gu = 0, tiles_dn = 0;
+    int32_t base = 0, tiles_gu = 0, tiles_dn = 0, used = 0, row_tiles = 0;
     for (int g0 = 0; g0 <= a.n_local; g0 += 64) {
         const int g = g0 + lane;
         const int32_t R = g < G ? tot[g] : 0;
@@ -280,8 +287,8 @@ __device__ inline void group_layout(const RowsArgs& a, const int32_t* tot, int32
             if (publish) a.row_offsets[g] = base + inc - R;
         }
         base += __builtin_amdgcn_readlane(inc, 63);
-        // the tile counts of the untiled GEMM paths
-        if (publish && !a.plan) {
+        // the tile counts of the GEMMs without a work list
+        if (publish && (!a.plan || a.choose)) {
             int32_t tg = 0, td = 0;
             if (g < G) {
                 const bool sh = g == a.n_local;
@@ -290,15 +297,21 @@ __device__ inline void group_layout(const RowsArgs& a, const int32_t* tot, int32
             }
             tiles_gu += __builtin_amdgcn_readlane(wave_scan_add(tg), 63);
             tiles_dn += __builtin_amdgcn_readlane(wave_scan_add(td), 63);
+            if (a.choose) {
+                used += __popcll(__builtin_amdgcn_ballot_w64(R > 0));
+                row_tiles += __builtin_amdgcn_readlane(wave_scan_add((R + a.bm_gu - 1) / a.bm_gu), 63);
+            }
         }
     }
+    const bool tiled = a.plan && !(a.choose && 4 * row_tiles <= 5 * used);
     if (publish && lane == 0) {
         a.row_offsets[a.n_local + 1] = base;
-        a.tile_info[0] = tiles_gu;
-        a.tile_info[1] = tiles_dn;
+        a.tile_info[0] = tiled ? 0 : tiles_gu;
+        a.tile_info[1] = tiled ? 0 : tiles_dn;
         a.tile_info[2] = base;
         a.tile_info[3] = 0;
     }
+    return tiled;
 }
 
 // x / n for x < 2^16 + 4 and n = 1 .. 4
@@ -389,7 +402,8 @@ __device__ inline PlanTry plan_tiles(const PlanShape& c, int R, int Rs, int lane
 
 // The work lists of both GEMMs: each of PW waves (4 or 8) tries tiles of one
 // height, for one GEMM (8) or both (4), and the wave with the least estimate of a
-// GEMM publishes.  publish_try, a barrier of the block, publish_best.
+// GEMM publishes (an empty list where the thin GEMMs take the batch).  publish_try,
+// a barrier of the block, publish_best.
 template <int PW>
 __device__ inline void publish_try(const RowsArgs& a, const int32_t* tot, int lane, int wave, float (*s_est)[4], PlanTry* o) {
     const int n = a.n_local;
@@ -403,7 +417,7 @@ __device__ inline void publish_try(const RowsArgs& a, const int32_t* tot, int la
 }
 template <int PW>
 __device__ inline void publish_best(const RowsArgs& a, const int32_t* tot, const int32_t* first, int lane, int wave,
-                                    const float (*s_est)[4], const PlanTry* o) {
+                                    const float (*s_est)[4], PlanTry* o, bool tiled) {
     const int n = a.n_local;
 #pragma unroll
     for (int i = 0; i < 8 / PW; ++i) {
@@ -415,6 +429,10 @@ __device__ inline void publish_best(const RowsArgs& a, const int32_t* tot, const
             if (s_est[w][j] < best) { best = s_est[w][j]; bw = j; }
         if (bw != (wave & 3)) continue;
         TilePlan* P = a.plan + w;
+        if (!tiled) {
+            o[i].rounds = o[i].items = o[i].sp0 = o[i].nsh = 0;
+            o[i].split = o[i].q = 1;
+        }
         if (lane == 0) {
             P->H = 4 - bw; P->rounds = o[i].rounds; P->items = o[i].items; P->sp0 = o[i].sp0; P->split = o[i].split;
             P->spread = o[i].spread; P->q = o[i].q; P->nsh = o[i].nsh;
@@ -469,7 +487,7 @@ __global__ void __launch_bounds__(FT_TB) rows_scatter_kernel(const RowsArgs a) {
         PlanTry o[2];
         publish_try<4>(a, s_tot, lane, wave, s_est, o);
         __syncthreads();
-        publish_best<4>(a, s_tot, s_first, lane, wave, s_est, o);
+        publish_best<4>(a, s_tot, s_first, lane, wave, s_est, o, true);
         return;
     }
     int grp[MAXR], rank[MAXR];
@@ -514,6 +532,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) rows_small_kernel(const RowsArgs
     __shared__ unsigned long long s_msk[SCAN_WAVES][MAXG];
     __shared__ int32_t s_first[MAXG], s_tot[MAXG];
     __shared__ float s_est[2][4];
+    __shared__ int s_tiled;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = a.n_local + a.has_shared;
     const int64_t t = tid;
@@ -544,10 +563,13 @@ __global__ void __launch_bounds__(SCAN_THREADS) rows_small_kernel(const RowsArgs
     constexpr int PW0 = SCAN_WAVES - 8;
     const bool planner = a.plan && wave >= PW0;
     PlanTry o[1];
-    if (wave == 0) group_layout(a, s_tot, s_first, lane, true);
+    if (wave == 0) {
+        const bool tiled = group_layout(a, s_tot, s_first, lane, true);
+        if (lane == 0) s_tiled = tiled;
+    }
     if (planner) publish_try<8>(a, s_tot, lane, wave - PW0, s_est, o);
     __syncthreads();
-    if (planner) publish_best<8>(a, s_tot, s_first, lane, wave - PW0, s_est, o);
+    if (planner) publish_best<8>(a, s_tot, s_first, lane, wave - PW0, s_est, o, s_tiled != 0);
     if (t < a.T) {
         const int stride = a.k + 1;
 #pragma unroll
@@ -1612,10 +1634,17 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 // (f >= TILED_F): 2 experts of f = 14336, 128 tokens, 1, 2 x 2 and 2 x 32 rows: thin
 // 82, 124 and 157 us, tiled 85, 119 and 123; f = 12288: tiled at most the time that
 // thin takes, f = 7168: 79 against 68 with few rows.
-// Above, up to THIN_SPARSE_T tokens, a mean of at most THIN_ROWS rows per expert: 128
-// experts of d = 4096 top-8, 140 tokens 226 us thin and 249 tiled, 256 tokens 239
-// and 254.
-constexpr int64_t THIN_MAX_T = 128, THIN_SPARSE_T = 512;
+// Above, with a mean of at most THIN_ROWS rows per expert: a layer of less than
+// STREAM_BYTES up to THIN_SMALL_T tokens, where thin is faster whatever the rows (8
+// experts of d = 1024, f = 640, 140 tokens: even rows 22 against 30 us, five experts
+// of 140 rows 30 and 34; 200 tokens: five of 200, 37 and 35).  In a larger one up to
+// THIN_SPARSE_T tokens the rows that the experts do get decide on the device
+// (group_layout): both are launched, and the one that is not wanted finds no tiles,
+// which costs 5 us.  Routing that leaves few rows per expert gains (32 of 128
+// experts of d = 4096, f = 1536, 140 to 320 tokens, even rows: 200 to 207 us, tiled
+// alone 216 to 222), hot experts pay only these (8 of 320 rows: 149 us, thin 325,
+// tiled alone 145).
+constexpr int64_t THIN_MAX_T = 128, THIN_SMALL_T = 160, THIN_SPARSE_T = 512;
 constexpr int THIN_ROWS = 20, TILED_F = 12288;
 // Routed gate/up weights of at least this many bytes are streamed with non-temporal
 // loads by short single row tiles and by the thin GEMM.  Tiled gate/up: 805 MB (32
@@ -1660,28 +1689,29 @@ size_t forward_split_floats(int gemms) {
 
 int forward_tokens_per_block() { return FT_TB; }
 
-int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, bool room) {
+int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, int64_t gu_bytes, bool room) {
     if (dtype != ORDERMOE_BF16) return 0;
     const bool few = T * k <= (int64_t)THIN_ROWS * E;
     if (T <= THIN_MAX_T) return few || f < TILED_F || n_shared >= 2 || !room ? GEMM_THIN : GEMM_TILED;
-    return few && T <= THIN_SPARSE_T && n_shared < 2 ? GEMM_THIN : GEMM_TILED;
+    if (!few || T > THIN_SPARSE_T || n_shared >= 2) return GEMM_TILED;
+    if (gu_bytes < STREAM_BYTES) return T <= THIN_SMALL_T || !room ? GEMM_THIN : GEMM_TILED;
+    return room ? GEMM_THIN | GEMM_TILED : GEMM_THIN;
 }
 
 int launch_local_forward(const ForwardArgs& f, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     const int has_sh = f.n_shared > 0 ? 1 : 0;
     const int G = f.n_local + has_sh;
-    const bool thin = f.gemms & GEMM_THIN;
-    // tile geometry (of the tiled bf16 GEMMs the shortest tile, for the grids)
-    const bool bf = f.dtype == ORDERMOE_BF16;
-    const int bm_gu = thin ? TH_BM : bf ? 64 : F32_BM, bm_dn = bm_gu;
-    const int bn_gu = thin ? TH_BN : bf ? TP_BN : F32_BN, bn_dn = bn_gu;
+    const bool thin = f.gemms & GEMM_THIN, tiled = f.gemms & GEMM_TILED;
     const int64_t rows_r = f.rmax_routed, rows_s = has_sh ? f.T : 0;
-    // upper bounds of the tiles, for the grids
-    const int64_t ub_gu = ((rows_r + bm_gu - 1) / bm_gu + f.n_local) * (2 * f.f / bn_gu) +
-                          (has_sh ? ((rows_s + bm_gu - 1) / bm_gu + 1) * (2 * f.n_shared * f.f / bn_gu) : 0);
-    const int64_t ub_dn = ((rows_r + rows_s + bm_dn - 1) / bm_dn + G) * (f.d / bn_dn);
-    const bool tiled = f.gemms & GEMM_TILED;
+    // upper bounds of the tiles, for the grids (of the tiled bf16 GEMMs: of the shortest tiles)
+    auto ub_gu = [&](int bm, int bn) {
+        return ((rows_r + bm - 1) / bm + f.n_local) * (2 * f.f / bn) +
+               (has_sh ? ((rows_s + bm - 1) / bm + 1) * (2 * f.n_shared * f.f / bn) : 0);
+    };
+    auto ub_dn = [&](int bm, int bn) { return ((rows_r + rows_s + bm - 1) / bm + G) * (f.d / bn); };
+    // tiles of the GEMMs without a work list
+    const int bm = thin ? TH_BM : F32_BM, bn = thin ? TH_BN : F32_BN;
     TilePlan* plan = tiled ? (TilePlan*)(f.sk_part + (size_t)(SK_MAX_GRID - 1) * 256 * TP_BN) : nullptr;
 
     RowsArgs r;
@@ -1691,9 +1721,10 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     r.blk_rows = f.blk_rows; r.row_offsets = f.row_offsets;
     r.row_tok = f.row_tok; r.row_w = f.row_w; r.tok_rows = f.tok_rows; r.tile_info = f.tile_info;
     r.sk_cnt = f.sk_cnt; r.nblk = f.nblk;
-    r.bm_gu = bm_gu; r.bn_gu = bn_gu; r.bm_dn = bm_dn; r.bn_dn = bn_dn;
+    r.bm_gu = r.bm_dn = bm; r.bn_gu = r.bn_dn = bn;
     r.n_gu_r = 2 * f.f; r.n_gu_s = 2 * f.n_shared * f.f; r.n_dn = f.d;
     r.plan = plan;
+    r.choose = thin && tiled;
     for (int w = 0; w < 2; ++w) {
         PlanShape& c = r.shape[w];
         c.nt_r = (w == 0 ? r.n_gu_r : r.n_dn) / TP_BN;
@@ -1701,7 +1732,7 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
         c.kt_r = (w == 0 ? f.d : f.f) / 64;
         c.kt_s = (w == 0 ? f.d : f.n_shared * f.f) / 64;
         c.q = has_sh && c.kt_s >= 2 * c.kt_r ? (c.kt_s / c.kt_r < SK_SPLIT ? c.kt_s / c.kt_r : SK_SPLIT) : 1;
-        c.grid = bf16_grid(w == 0 ? ub_gu : ub_dn);
+        c.grid = bf16_grid(w == 0 ? ub_gu(64, TP_BN) : ub_dn(64, TP_BN));
         c.grid_inv = (uint32_t)(((1ull << 32) + c.grid - 1) / c.grid);
     }
 
@@ -1737,47 +1768,29 @@ int launch_local_forward(const ForwardArgs& f, void* stream) {
     g.ntiles = f.tile_info + 0;
     g.Nr = 2 * f.f; g.Kr = f.d; g.Ns = 2 * f.n_shared * f.f; g.Ks = f.d;
     g.Wr = f.w_gu; g.Ws = f.w_sh_gu; g.Ar = nullptr; g.As = nullptr; g.Or = f.act_r; g.Os = f.act_s;
-    if (thin) {
-        {
+    {
         KernelTimer kt_("gemm_gate_up", st);
-        ggemm_thin<0><<<dim3(persistent_grid(ub_gu, THIN_PER_CU)), dim3(256), 0, st>>>(g);
+        if (thin) ggemm_thin<0><<<dim3(persistent_grid(ub_gu(bm, bn), THIN_PER_CU)), dim3(256), 0, st>>>(g);
+        if (tiled) {
+            g.plan = plan;
+            ggemm_bf16<0><<<dim3(r.shape[0].grid), dim3(256), 0, st>>>(g);
         }
-        if ((e = hipGetLastError()) != hipSuccess) return (int)e;
-    } else if (f.dtype == ORDERMOE_BF16) {
-        {
-        KernelTimer kt_("gemm_gate_up", st);
-        g.plan = plan;
-        ggemm_bf16<0><<<dim3(r.shape[0].grid), dim3(256), 0, st>>>(g);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return (int)e;
-    } else {
-        {
-        KernelTimer kt_("gemm_gate_up", st);
-        ggemm_f32<0><<<dim3(persistent_grid(2 * ub_gu, F32_PER_CU)), dim3(F32_THREADS), 0, st>>>(g);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return (int)e;
+        if (!f.gemms) ggemm_f32<0><<<dim3(persistent_grid(2 * ub_gu(bm, bn), F32_PER_CU)), dim3(F32_THREADS), 0, st>>>(g);
     }
+    if ((e = hipGetLastError()) != hipSuccess) return (int)e;
 
     // down: activations [rows][f] x [d][f]^T -> row outputs [rows][d], scaled by the gate
     g.ntiles = f.tile_info + 1;
     g.Nr = f.d; g.Kr = f.f; g.Ns = f.d; g.Ks = f.n_shared * f.f;
     g.Wr = f.w_dn; g.Ws = f.w_sh_dn; g.Ar = f.act_r; g.As = f.act_s; g.Or = f.obuf; g.Os = nullptr;
-    if (thin) {
-        {
+    {
         KernelTimer kt_("gemm_down", st);
-        ggemm_thin<1><<<dim3(persistent_grid(ub_dn, THIN_PER_CU)), dim3(256), 0, st>>>(g);
+        if (thin) ggemm_thin<1><<<dim3(persistent_grid(ub_dn(bm, bn), THIN_PER_CU)), dim3(256), 0, st>>>(g);
+        if (tiled) {
+            g.plan = plan + 1;
+            ggemm_bf16<1><<<dim3(r.shape[1].grid), dim3(256), 0, st>>>(g);
         }
-    } else if (f.dtype == ORDERMOE_BF16) {
-        {
-        KernelTimer kt_("gemm_down", st);
-        g.plan = plan + 1;
-        ggemm_bf16<1><<<dim3(r.shape[1].grid), dim3(256), 0, st>>>(g);
-        }
-    } else {
-        {
-        KernelTimer kt_("gemm_down", st);
-        ggemm_f32<1><<<dim3(persistent_grid(2 * ub_dn, F32_PER_CU)), dim3(F32_THREADS), 0, st>>>(g);
-        }
+        if (!f.gemms) ggemm_f32<1><<<dim3(persistent_grid(2 * ub_dn(bm, bn), F32_PER_CU)), dim3(F32_THREADS), 0, st>>>(g);
     }
     if ((e = hipGetLastError()) != hipSuccess) return (int)e;
 

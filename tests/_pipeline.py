@@ -290,6 +290,29 @@ def with_horizon(sc: StreamCase, H: int, allow_sub: Optional[int] = None) -> Str
     return dataclasses.replace(sc, cfg=cfg, phi=phi, S=S)
 
 
+# ------------------------------------------------------------ published GEMM work lists
+PARTIAL_TILES = 64 << 20       # bytes of partial tiles at the end of a workspace of the tiled bf16 GEMMs
+
+
+def published_plans(ws):
+    """What the row kernels of the last forward in `ws` (a uint8 tensor of exactly
+    the size asked for) published for the tiled gate/up and down GEMMs: tile
+    height in rows (H 64), whole rounds of the grid, work items, the first item
+    cut along K and into how many pieces, K pieces of a shared tile, shared tiles,
+    and per group (the shared one last) its rows and tiles.  The lists lie in the
+    place of the last partial tile."""
+    import torch
+    words = 8 + 4 * 65                                       # TilePlan: eight fields, 64 + 1 groups of four
+    raw = ws[-256 * 256 * 4:][:2 * words * 4].view(torch.int32).cpu().numpy().reshape(2, words)
+    out = []
+    for p in raw:
+        plan = dict(zip(("H", "rounds", "items", "sp0", "split", "spread", "q", "nsh"), (int(v) for v in p[:8])))
+        plan["groups"] = [dict(first=int(a), tiles=int(b) >> 3, last=int(b) & 7, off=int(c), rows=int(r))
+                          for a, b, c, r in p[8:].reshape(65, 4)]
+        out.append(plan)
+    return out
+
+
 # ------------------------------------------------------------ GEMM work plan (host mirror)
 # The bf16 grouped GEMMs of the local forward (batches above 128 tokens) run
 # 256 x 256 gate/up tiles and 192 x 256 down tiles over a persistent grid of at

@@ -292,6 +292,20 @@ def test_batches_of_128_tokens_need_no_partial_tiles(d, f, E, k, n_shared):
     assert size(513) > PARTIAL_TILES
 
 
+def test_sparse_batches_of_large_layers_have_room_for_both_gemms():
+    """Above 128 tokens, at most 20 rows per expert by the mean: the rows decide on
+    the device in a layer of 64 MiB of routed gate/up weights, and a smaller one
+    takes the thin GEMM up to 160 tokens."""
+    def size(T, n_local):
+        ids = np.arange(n_local, dtype=np.int32)
+        ex = om.Experts(dtype=om.BF16, d=2048, f=512, E=128, n_local=n_local, n_shared=0)
+        ex.local_experts = ids.ctypes.data_as(ctypes.c_void_p)
+        ex.w_gate_up = ex.w_down = 16
+        return om.ordermoe_forward_workspace_size(ex, T, 8)
+    for T, n_local, room in ((128, 16, False), (129, 16, True), (320, 16, True), (160, 15, False), (161, 15, True)):
+        assert (size(T, n_local) > PARTIAL_TILES) == room, (T, n_local)
+
+
 def test_forward_rejects_operands_past_31_bit_offsets():
     """The GEMMs address operands with 32-bit byte offsets: T*d*esz, 2*f*d*esz,
     2*n_shared*f*d*esz and T*n_shared*f*esz must stay below 2^31 (no launch)."""
