@@ -184,6 +184,7 @@ class DeviceLayer:
                          dtype=torch.uint8, device="cuda")
         om.ordermoe_local_moe_forward(self.experts, x, T, self.cfg.k, out["w"], out["exec_k"],
                                       out["exec_m"], loc, server, y, ro, ws)
+        self.ws = ws                   # the last forward's: holds what published_plans reads
         return y, ro
 
 
@@ -311,49 +312,3 @@ def published_plans(ws):
                           for a, b, c, r in p[8:].reshape(65, 4)]
         out.append(plan)
     return out
-
-
-# ------------------------------------------------------------ GEMM work plan (host mirror)
-# The bf16 grouped GEMMs of the local forward (batches above 128 tokens) run
-# 256 x 256 gate/up tiles and 192 x 256 down tiles over a persistent grid of at
-# most 256 workgroups (one per CU on MI355X, at most four per tile); the tiles
-# left after whole rounds are cut along K into up to 4 pieces of at least 16 K
-# tiles of 64 when at least two workgroups per tile are free and every group
-# has the same K.  Tests use this
-# mirror to know which of their shapes exercise the split.
-def gemm_plan(cfg, rows, n_local: int, cus: int = 256):
-    """rows: the forward's row_offsets output [n_local + 2].  Returns
-    {"gate_up": (tiles, grid, rounds, left, split, shared_halves, tile_rows), "down": (...)};
-    shared_halves is 1 when the shared tiles are cut into two K halves."""
-    R = np.diff(np.asarray(rows, dtype=np.int64))       # rows per group, shared last
-    has_sh = cfg.n_shared > 0
-    T, k, d, f, ns = cfg.T, cfg.k, cfg.d, cfg.f, cfg.n_shared
-    rr = T * min(k, n_local)
-    rs = T if has_sh else 0
-
-    def grid_of(ub):
-        g = min(cus, 4 * ub)
-        g = (g + 7) & ~7
-        return min(max(g, 8), 256)
-
-    def plan(bm, bn, Nr, Ns, Kr, Ks, ub):
-        tiles = sum(-(-int(R[g]) // bm) * (Nr // bn) for g in range(n_local))
-        if has_sh:
-            tiles += -(-int(R[n_local]) // bm) * (Ns // bn)
-        grid = grid_of(ub)
-        nsh = -(-int(R[n_local]) // bm) * (Ns // bn) if has_sh else 0
-        halves = int(nsh > 0 and Ks >= 2 * Kr and Ks % 256 == 0 and 2 * nsh <= grid)
-        items = tiles + nsh * halves
-        rounds = items // grid
-        left = items - rounds * grid
-        split = min(grid // left, 4, Kr // 128, Kr // 64 // 16) if left else 0
-        if has_sh and Ks != Kr:
-            split = 1
-        return tiles, grid, rounds, left, split, halves, bm
-
-    ub_gu = (-(-rr // 256) + n_local) * (2 * f // 256) + ((-(-rs // 256) + 1) * (2 * ns * f // 256) if has_sh else 0)
-    # down tiles of 256 rows when even those would fill the grid eight times over
-    bm_dn = 256 if (-(-(rr + rs) // 256) + n_local + int(has_sh)) * (d // 256) >= 8 * 256 else 192
-    ub_dn = (-(-(rr + rs) // bm_dn) + n_local + int(has_sh)) * (d // 256)
-    return {"gate_up": plan(256, 256, 2 * f, 2 * ns * f, d, d, ub_gu),
-            "down": plan(bm_dn, 256, d, d, f, ns * f, ub_dn)}

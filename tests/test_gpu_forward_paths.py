@@ -105,3 +105,58 @@ def test_sparse_batches_choose_their_gemms_by_the_rows(rows, n_shared, here, til
     z, _ = l.run(l.need - PARTIAL_TILES)
     assert l.error(z) <= ERROR
     assert tiled or torch.equal(y, z)
+
+
+@pytest.mark.parametrize("rows,d,f,n_shared,here,gate_up,down", [
+    # shared tiles in K pieces and left-over routed tiles cut in the same launch: slots and counters of both
+    ([15] * 32, 2048, 2048, 2, 40, {}, dict(q=2, split=3, rounds=1)),
+    # a cut 256-row tile (the shared group's), gate/up and down, in two to four pieces
+    ([39, 29, 45, 48, 33], 1024, 128, 4, 194, dict(H=4, split=2), {}),
+    ([49, 50, 32, 49, 54], 2048, 128, 4, 223, dict(H=4, split=3), {}),
+    ([31, 30, 37, 32, 36, 29, 35, 51], 4096, 128, 1, 238, dict(H=4, split=4), {}),
+    ([50, 55, 40, 48, 54], 256, 1024, 1, 222, {}, dict(H=4, split=2)),
+    ([12, 8, 14, 16, 15, 16, 13, 15, 8, 15, 11, 10, 12, 15, 15, 15], 256, 2048, 1, 203, {}, dict(H=4, split=3)),
+    ([54, 38, 29, 47, 53], 256, 3072, 1, 199, {}, dict(H=4, split=4)),
+    # cut 128- and 64-row tiles
+    ([72, 75, 133, 107, 121, 97, 102, 92], 4096, 256, 4, 783, dict(H=2, split=3), {}),
+    ([133], 4096, 128, 1, 22, dict(H=1, split=4), {}),
+    # shared tiles in two, three and four K pieces beside whole rounds of routed ones
+    ([12] * 32, 2048, 512, 4, 191, {}, dict(q=2, rounds=1)),
+    ([128, 103], 4096, 512, 4, 193, {}, dict(q=3, rounds=1)),
+    ([196, 197], 2048, 1024, 4, 356, {}, dict(q=4, rounds=1)),
+])
+def test_work_lists_that_cut_tiles(rows, d, f, n_shared, here, gate_up, down):
+    l = Layer(rows, d, f, n_shared, here, T=sum(rows), E=len(rows), k=1)
+    y, ws = l.run()
+    for p, want in zip(published_plans(ws), (gate_up, down)):
+        print({n: v for n, v in p.items() if n != "groups"}, flush=True)
+        assert {n: p[n] for n in want} == want
+    assert l.error(y) <= ERROR
+    for _ in range(3):
+        assert torch.equal(y, l.run()[0])
+
+
+@pytest.mark.parametrize("T,k,E,d,f,n_shared,rows,path", [
+    (32, 4, 60, 512, 256, 4, [3, 9, 1], "thin"),
+    (33, 4, 60, 512, 256, 4, [3, 9, 1], "thin"),
+    (128, 6, 64, 512, 256, 2, [97, 31], "thin"),               # several row tiles, a shared K twice the routed one
+    (129, 6, 64, 512, 256, 2, [97, 31], "tiled"),
+    (129, 1, 7, 512, 256, 1, [97, 31], "thin"),                # 18.4 rows per expert
+    (160, 8, 64, 512, 256, 1, [150, 10], "thin"),              # 20 rows per expert, a small layer
+    (161, 8, 64, 512, 256, 1, [150, 10], "tiled"),
+    (161, 8, 65, 512, 256, 1, [150, 10], "tiled"),             # 19.8, small, above 160 tokens
+    (512, 5, 128, 2048, 512, 0, [32] * 16, "thin"),            # 20, 64 MiB of gate/up weights: by the rows
+    (512, 5, 128, 2048, 512, 0, [100, 412] + [0] * 14, "tiled"),
+    (513, 5, 129, 2048, 512, 0, [32] * 16, "tiled"),
+    (80, 2, 8, 256, 12288, 1, [70, 10], "thin"),               # wide experts: 20 rows per expert
+    (81, 2, 8, 256, 12288, 1, [70, 10], "tiled"),
+    (81, 2, 8, 256, 12288 - 128, 1, [70, 10], "thin"),
+    (81, 2, 8, 256, 12288, 2, [70, 10], "thin"),
+])
+def test_batches_on_either_side_of_the_rules(T, k, E, d, f, n_shared, rows, path):
+    l = Layer(rows, d, f, n_shared, T // 2 if n_shared else 0, T, E, k)
+    y, ws = l.run()
+    tiled = l.need > PARTIAL_TILES and published_plans(ws)[0]["items"] > 0
+    assert ("tiled" if tiled else "thin") == path
+    assert l.error(y) <= ERROR
+    assert torch.equal(y, l.run()[0])

@@ -11,8 +11,8 @@ import pytest
 import workloads as wl
 from oracle import layer as olayer
 
-from ._pipeline import (DeviceLayer, build_case, gemm_plan, host, library_tables, oracle_decisions,
-                        oracle_output)
+from ._pipeline import (PARTIAL_TILES, DeviceLayer, build_case, host, library_tables, oracle_decisions,
+                        oracle_output, published_plans)
 
 pytestmark = pytest.mark.gpu
 
@@ -44,14 +44,12 @@ SMALL = {
     "C4s_M12": wl.C4.with_(T=1700, T_cal=4096, M=12, capacity=(8.0,) * 12, loc_mode="uniform"),
     "C4s_M16": wl.C4.with_(T=1700, T_cal=4096, M=16, capacity=(8.0,) * 16, loc_mode="uniform"),
     "Cmax": CMAX,
-    # the leftover-tile split along K (pieces of at least 16 K tiles), with one
-    # shared expert so that the down projection's shared tiles have the routed K
-    # and split too: the down projection in 2 pieces with no whole round (128
-    # tiles), and the gate/up projection in 2 pieces after a whole round (312)
+    # tiles cut along K, see PLANS: the down projection of short groups in two
+    # pieces; 192-row gate/up tiles over a whole round and an uncut partial one
     "C3split": wl.C3.with_(T=600, d=2048, f=2048, n_shared=1, T_cal=4096),
     "C4split": wl.C4.with_(T=1200, d=2048, f=3072, n_shared=1, T_cal=4096),
     # four shared experts: the down projection's shared K is four times the
-    # routed K, so its shared tiles are cut into two K halves
+    # routed K, so its shared tiles are cut into K pieces
     "C3sh": wl.C3.with_(T=600, d=1024, f=512, n_shared=4, T_cal=4096),
     # 16-token routing blocks with their token rows staged in LDS (at most one
     # block per CU, d % 512 == 0), the last block holding 9 tokens
@@ -59,17 +57,23 @@ SMALL = {
     # the same path at its bounds: 16 experts, d = 4096, 16 rows of 8 KB per block
     "C2xl16": wl.C2.with_(T=4001, f=512, E=16, clusters=8, cluster_size=2, capacity=(8.0,) * 4,
                           T_cal=4096),
-    # a batch large enough for 256-row down tiles (the host's row bound fills
-    # the grid eight times over), over two whole rounds and a partial one
+    # 256-row down tiles over two whole rounds and a partial one
     "C4tall": wl.C4.with_(T=4700, d=4096, f=256, T_cal=4096),
 }
-# shapes whose GEMM plan splits leftover tiles along K (checked on the GPU's rows)
-SPLIT = {"C3split": {"gate_up": 0, "down": 2}, "C4split": {"gate_up": 2, "down": 1},
-         "C2": {"gate_up": 2}, "C2x": {"gate_up": 3}}
-# shapes whose down projection cuts its shared tiles into two K halves
-SHARED_HALVES = {"C3sh", "C3"}
-# shapes whose down projection takes 256-row tiles (large batches)
-TALL_DOWN = {"C4", "C4tall"}
+# what the work lists of the tiled shapes are meant to exercise (fields of
+# published_plans, for the rows that the GPU's own routing gives)
+PLANS = {
+    "C2s": {"gate_up": dict(H=3, rounds=1, split=1), "down": dict(H=3, rounds=0, split=4)},
+    "C3s": {"down": dict(q=2, split=1)},
+    "C3split": {"gate_up": dict(rounds=1), "down": dict(rounds=0, split=2, q=1)},
+    "C4split": {"gate_up": dict(H=3, rounds=1, split=1), "down": dict(H=2, split=1)},
+    "C3sh": {"gate_up": dict(split=2), "down": dict(q=3, split=1)},
+    "C4tall": {"down": dict(H=4, rounds=2, split=1)},
+    "C2": {"gate_up": dict(H=4, rounds=4, split=2), "down": dict(H=3)},
+    "C2x": {"gate_up": dict(H=3, rounds=10, split=1), "down": dict(H=2, rounds=2, split=3)},
+    "C3": {"gate_up": dict(H=4, rounds=2), "down": dict(H=2, rounds=1)},
+    "C4": {"gate_up": dict(H=4, rounds=9), "down": dict(H=4, rounds=4)},
+}
 # decode-sized batches (at most 128 tokens): the thin-GEMM path of the forward
 DECODE = {
     "C2d": wl.C2.with_(T=64, T_cal=4096),
@@ -152,19 +156,25 @@ def _check_output(case, dec, y_gpu, tokens, ok, tol):
     assert worst <= tol
 
 
-def _check_split(name, case, rows):
-    """The shapes meant to exercise the split along K do split (host mirror of
-    the launch plan, from the GPU's own row counts)."""
-    if name not in SPLIT and name not in SHARED_HALVES and name not in TALL_DOWN:
+def _check_plan(name, case, dl, rows):
+    """The work lists that the row kernels published cover the rows, and the shapes
+    meant to exercise a cut, a height or several rounds do."""
+    if case.cfg.dtype != "bf16":
         return
-    plan = gemm_plan(case.cfg, rows, len(case.local))
-    print("[%s] GEMM plan (tiles, grid, rounds, left, split, shared halves, tile rows): %s"
-          % (case.cfg.name, plan), flush=True)
-    assert plan["down"][6] == (256 if name in TALL_DOWN else 192), plan["down"]
-    for gemm, want in SPLIT.get(name, {}).items():
-        assert plan[gemm][4] == want, (gemm, plan[gemm])
-    assert plan["down"][5] == int(name in SHARED_HALVES), plan["down"]
-    assert plan["gate_up"][5] == 0, plan["gate_up"]
+    plans = dict(zip(("gate_up", "down"), published_plans(dl.ws)))
+    counts = np.diff(rows)
+    for gemm, p in plans.items():
+        print("[%s] %s: %s" % (case.cfg.name, gemm, {n: v for n, v in p.items() if n != "groups"}), flush=True)
+        for g, R in enumerate(counts):
+            seg = p["groups"][g]
+            assert seg["rows"] == R
+            if R:
+                assert seg["off"] == rows[g]
+                assert 1 <= seg["last"] <= p["H"] and (seg["tiles"] - 1) * p["H"] + seg["last"] == -(-R // 64)
+            else:
+                assert seg["tiles"] == 0
+        for field, want in PLANS.get(name, {}).get(gemm, {}).items():
+            assert p[field] == want, (gemm, field, p[field])
 
 
 @pytest.mark.parametrize("name", list(SMALL))
@@ -181,7 +191,7 @@ def test_layer_parity_small(name):
     # row offsets: the GPU's own local rows, recounted from its decisions
     rows = host(ro)
     assert rows[0] == 0 and np.all(np.diff(rows) >= 0)
-    _check_split(name, case, rows)
+    _check_plan(name, case, dl, rows)
     _check_output(case, dec, y, np.arange(T), ok, TOL[case.cfg.dtype])
 
 
@@ -196,6 +206,7 @@ def test_layer_parity_decode_batch(name):
     torch.cuda.synchronize()
     dec = oracle_decisions(case)
     ok = _check_decisions(case, dec, out)
+    assert dl.ws.numel() < PARTIAL_TILES                          # the thin GEMMs alone
     _check_output(case, dec, y, np.arange(T), ok, TOL[case.cfg.dtype])
 
 
@@ -212,7 +223,7 @@ def test_layer_parity_full_shape(name):
     torch.cuda.synchronize()
     dec = oracle_decisions(case)
     ok = _check_decisions(case, dec, out)
-    _check_split(name, case, host(ro))
+    _check_plan(name, case, dl, host(ro))
     _check_output(case, dec, y, np.arange(T), ok, TOL[case.cfg.dtype])
 
 

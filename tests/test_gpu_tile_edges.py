@@ -1,7 +1,7 @@
-"""The bf16 tiled forward (batches above 128 tokens) where its work list can go
-wrong: row counts at the edges of the 64-row units and of the tile heights,
-empty groups, shared tiles cut into K pieces beside whole routed tiles, several
-rounds of the grid with pieces left over.  Against fp64, through the C ABI."""
+"""The bf16 tiled forward where its work list can go wrong: row counts at the
+edges of the 64-row units and of the tile heights, empty groups, shared tiles cut
+into K pieces beside whole routed tiles, tiles of several heights over several
+rounds of the grid.  Against fp64, through the C ABI."""
 import numpy as np
 import pytest
 
@@ -18,9 +18,9 @@ from paper_2607_17154_amd import ordermoe as om  # noqa: E402
     ([129], 256, 128, 0, 0),                            # the smallest matrices: one column tile, 2 K tiles
     ([63, 64, 65, 1, 0, 128, 129], 256, 256, 0, 0),     # unit edges, an empty group between others
     ([192, 193, 255, 256, 257, 0], 512, 384, 1, 130),   # height edges, the last group empty, shared K = routed K
-    ([0, 40, 300], 512, 256, 4, 321),                   # shared K four times the routed K: four pieces
-    ([700, 20, 513], 2048, 1024, 2, 900),               # long K: pieces of shared and of left-over tiles
-    ([5000, 300, 4000, 33], 512, 2048, 2, 3000),        # several rounds in both GEMMs, ragged ends
+    ([0, 40, 300], 512, 256, 4, 321),                   # shared K four times the routed K, in whole tiles
+    ([700, 20, 513], 2048, 1024, 2, 900),               # long K: shared down tiles in two K pieces
+    ([5000, 300, 4000, 33], 512, 2048, 2, 3000),        # gate/up tiles of three heights over three rounds and a partial one, ragged ends
     ([20] * 64, 256, 128, 1, 1280),                     # as many groups as fit, all in 64-row tiles
 ])
 def test_bf16_forward_at_the_tile_edges(rows, d, f, n_shared, here):
