@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(LD_THREADS) lookahead_depth_kernel(const LookA
     }
     double* s_v0 = s_la;                                   // [M][E] delay part of the cost
     double* s_nxt = s_la + ME;                             // [M][E] Phi^(h-1) of layer l + 1
-    double* s_P = s_la;                                    // [E][LA_PC + 1], after the minima
+    double* s_P = s_la;                                    // [E][LA_LP], after the minima
     double* s_V = s_la + lookahead_lds_cost(E, M);         // [E]
     const int NW = (E + 63) >> 6;                          // 64-expert words of a member mask
     uint64_t* s_mem = (uint64_t*)(s_V + E);                // [E][NW] members of each expert's group

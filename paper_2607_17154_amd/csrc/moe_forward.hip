@@ -16,6 +16,8 @@
 //                        packed [2f][d] weights, epilogue silu(g) * u -> bf16
 //   ggemm_bf16<.., 1>    down projection of the activations, epilogue scales
 //                        each row by its gate weight -> bf16 row outputs
+//   ggemm_thin<0, 1>     the same two for batches with few rows per expert
+//   ggemm_f32<0, 1>      the same two for fp32 storage
 //   combine_kernel       y[t] = sum of t's row outputs in slot order (fp32)
 // The GEMMs are persistent: each workgroup walks a tile list made on the device
 // (row counts are never read by the host).  Tiles of one expert are ordered
@@ -358,7 +360,7 @@ __device__ inline PlanTry plan_tiles(const PlanShape& c, int R, int Rs, int lane
         }
         // whole rounds, then the items left over; the routed ones of these are cut
         // along K into `split` pieces when that ends the launch sooner
-        // (fewer than 2^20 items, so the multiplication is exact)
+        // (fewer than 2^21 items, so the multiplication is exact)
         const int rounds = (int)__umulhi((uint32_t)items, c.grid_inv), head = rounds * c.grid, left = items - head;
         const int sp0 = q > 1 && sh_items > head ? sh_items : head, ns = items - sp0, whole = sp0 - head;
         const float mean = items > 0 ? sum * __builtin_amdgcn_rcpf((float)items) : 0.f;

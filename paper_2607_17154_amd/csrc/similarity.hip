@@ -511,9 +511,10 @@ __global__ void __launch_bounds__(256) sim_partial_kernel(const SimArgs a) {
 // 16 lanes per token) and the Gram update, fp32 FMAs in token order with SE * SE
 // entries spread over the threads (SE: experts rounded up to a power of two, at
 // least 16).  A partial holds SE x SE floats, so that few experts leave room in
-// the workspace for one partial per SE tokens: 128 blocks for 2048 tokens of 8
-// experts, where chunks of 128 tokens gave 16 blocks with a serial fp64 chain
-// per logit (272 us; now 8.5 us).
+// the workspace for one partial per SE tokens up to 32768 tokens (beyond, a
+// partial sums SE T / 32768 fp32 products per entry, never more than chunks of 128
+// tokens did): 128 blocks for 2048 tokens of 8 experts, where chunks of 128 tokens
+// gave 16 blocks with a serial fp64 chain per logit (272 us; now 7.2 us).
 template <int SE>
 __global__ void __launch_bounds__(LF_THREADS) sim_f32_kernel(const SimArgs a) {
     constexpr int LD = SE + 4;
@@ -594,9 +595,9 @@ __global__ void __launch_bounds__(LF_THREADS) sim_f32_kernel(const SimArgs a) {
 }
 
 // Fixed-order fp64 sum of the per-block partial Gram matrices (se x se floats
-// each) and counts.  A block of 1024 threads takes 64 consecutive entries; thread (s, c) adds the
-// parts s, s + 16, ... of entry c (independent loads, coalesced over c), then
-// the 16 slices are added in slice order.
+// each) and counts.  A block of 1024 threads takes 64 consecutive entries; thread
+// (s, c) adds the parts s, s + 16, ... of entry c (independent loads, coalesced over
+// c), then the 16 slices are added in slice order.
 constexpr int RED_SLICES = 16, RED_COLS = 64;
 
 __global__ void __launch_bounds__(RED_SLICES * RED_COLS) sim_reduce_kernel(const SimArgs a, int nparts, int se,
