@@ -438,9 +438,9 @@ typedef struct {
  * GEMM tiles split along K (summed in K order, so results are deterministic) and
  * the GEMMs' work lists: T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E,
  * and T > 128, except T <= 160 where n_shared < 2, T k <= 20 E and the routed
- * gate/up weights take less than 64 MiB.  (A workspace smaller by the 64 MiB is accepted, and the batch takes
- * the untiled GEMMs, where T <= 128, and where T <= 512, n_shared < 2 and
- * T k <= 20 E.)  The
+ * gate/up weights take less than 64 MiB.  (A workspace smaller by the 64 MiB is
+ * accepted, and the batch takes the untiled GEMMs, where T <= 128, and where
+ * T <= 512, n_shared < 2 and T k <= 20 E.)  The
  * call uses it until the stream passes the call; calls in flight at the same
  * time need workspaces of their own. */
 size_t ordermoe_forward_workspace_size(const ordermoe_experts* W, int64_t T, int32_t k);

@@ -1655,8 +1655,9 @@ constexpr int THIN_ROWS = 20, TILED_F = 12288;
 // loads forfeit: 21 MB (8 of d = 1024, f = 640) 15 -> 19 us.  Thin, the whole layer
 // at 4 and 64 tokens: over three layers in turn 92 MB and 173 MB (15 of d = 2048,
 // f = 1408) 2 to 5% faster, 21 MB 5 to 8% slower; over one layer of 92 MB again and
-// again, which then stays in the caches, 6% slower.  (In the down GEMM the further tile variants
-// spilled: 78 -> 85 us at the first shape; it keeps ordinary loads.)
+// again, which then stays in the caches, 6% slower.  (In the tiled down GEMM the
+// further tile variants spilled: 78 -> 85 us at the first shape; it keeps ordinary
+// loads.)
 constexpr int64_t STREAM_BYTES = 64 << 20;
 constexpr int THIN_PER_CU = 3;
 
