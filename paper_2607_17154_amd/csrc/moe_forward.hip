@@ -1633,9 +1633,10 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 // experts of d = 2048, f = 1408, one row: 24 us thin, 36 tiled), the thin one at
 // most twice as long when a few experts get all tokens.  Except where THIN_ROWS rows
 // per expert are the mean and one expert's gate/up tiles fill half the chip
-// (f >= TILED_F): 2 experts of f = 14336, 128 tokens, 1, 2 x 2 and 2 x 32 rows: thin
-// 82, 124 and 157 us, tiled 85, 119 and 123; f = 12288: tiled at most the time that
-// thin takes, f = 7168: 79 against 68 with few rows.
+// (f >= TILED_F): 2 experts of f = 14336, 128 tokens, three layers in turn, 2 x 2, 2 x
+// 32 and 2 x 128 rows: thin 136, 166 and 319 us, tiled 135, 141 and 159 (and 90 against
+// 102 at a single row); f = 12288: tiled at most the time that thin takes, f = 7168: 79
+// against 68 with few rows.
 // Above, with a mean of at most THIN_ROWS rows per expert: a layer of less than
 // STREAM_BYTES up to THIN_SMALL_T tokens, where thin is faster whatever the rows (8
 // experts of d = 1024, f = 640, 140 tokens: even rows 22 against 30 us, five experts
