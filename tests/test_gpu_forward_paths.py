@@ -160,3 +160,43 @@ def test_batches_on_either_side_of_the_rules(T, k, E, d, f, n_shared, rows, path
     assert ("tiled" if tiled else "thin") == path
     assert l.error(y) <= ERROR
     assert torch.equal(y, l.run()[0])
+
+
+def test_a_captured_sparse_batch_follows_its_rows():
+    """The choice of the GEMMs is made on the device, so one graph serves batches of
+    either kind: each replay equals the eager call on the same rows."""
+    rows = [18] * 16
+    l = Layer(rows, 2048, 512, 0, 0, T=300, E=16, k=1)
+    even, hot = l.ek.clone(), torch.full_like(l.ek, 3)
+    hot[l.m == 1] = 15
+    ws = torch.empty(l.need, dtype=torch.uint8, device="cuda")
+    y, ro = torch.empty((l.T, l.d), dtype=BF, device="cuda"), torch.empty(l.n + 2, dtype=torch.int32, device="cuda")
+    ek = even.clone()
+
+    def step():
+        om.ordermoe_local_moe_forward(l.ex, l.x, l.T, l.k, l.w, ek, l.m, l.loc, 0, y, ro, ws)
+
+    want = []
+    for src in (even, hot):
+        ek.copy_(src)
+        step()
+        torch.cuda.synchronize()
+        want.append((y.clone(), published_plans(ws)[0]["items"] > 0))
+    assert [t for _, t in want] == [False, True]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for i in (0, 1, 1, 0, 1):
+        ek.copy_((even, hot)[i])
+        y.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[i][0]) and (published_plans(ws)[0]["items"] > 0) == want[i][1]
+    del g

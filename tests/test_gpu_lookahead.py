@@ -118,3 +118,50 @@ def test_device_tables_equal_the_host_at_the_edges(N, E, M, T, H, pin, allow_sub
     want = om.ordermoe_build_lookahead(H, *args, 0.5, 0.5, 0.25, pin, allow_sub)
     got = om.ordermoe_build_lookahead_device(H, *(_dev(a) for a in args), 0.5, 0.5, 0.25, pin, allow_sub)
     np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
+def test_captured_tables_equal_the_eager_ones():
+    """Both builds in one graph (128 experts, whose staged rows need more LDS than a
+    kernel has by default): each replay, with other inputs, equals the host's."""
+    N, E, M, T, H = 4, 128, 8, 900, 3
+    rng = np.random.default_rng(5)
+
+    def inputs():
+        top1 = rng.integers(0, E, size=(N, T)).astype(np.int32)
+        x = (rng.random((N, M, E)) < 0.3).astype(np.uint8)
+        x[:, rng.integers(0, M, E), np.arange(E)] = 1
+        return [top1, x, rng.uniform(0.3, 1.0, (N, E, E)).astype(np.float32), rng.integers(0, E // 7, size=(N, E)).astype(np.int32),
+                rng.uniform(0.4, 0.8, N).astype(np.float32), rng.uniform(1e5, 1e6, N), rng.uniform(1e9, 1e10, (N, E)),
+                rng.uniform(1e-5, 1e-4, N), rng.uniform(1e9, 1e10, (M, M)), rng.uniform(1e-4, 1e-2, (M, M)), rng.uniform(2e13, 1e14, M)]
+
+    dev = [_dev(a) for a in inputs()]
+    P, phi = (torch.empty(s, dtype=torch.float64, device="cuda") for s in ((N - 1, E, E), (N, M, E)))
+    L = om.lib()
+    ws_t, ws_l = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (L.ordermoe_transitions_device_workspace_size(N, E),
+                                                                            L.ordermoe_lookahead_device_workspace_size(N, E, M)))
+
+    def step():
+        om.ordermoe_estimate_transitions_device(dev[0], E, P=P, ws=ws_t)
+        om.ordermoe_build_lookahead_device(H, P, *dev[1:], 0.5, 0.5, 0.25, 1, 1, phi=phi, ws=ws_l)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for _ in range(3):
+        new = inputs()
+        for d, a in zip(dev, new):
+            d.copy_(torch.from_numpy(a))
+        phi.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        P_host = om.ordermoe_estimate_transitions(new[0], E)
+        np.testing.assert_array_equal(P.cpu().numpy(), P_host)
+        np.testing.assert_array_equal(phi.cpu().numpy(), om.ordermoe_build_lookahead(H, P_host, *new[1:], 0.5, 0.5, 0.25, 1, 1))
+    del g
