@@ -436,9 +436,10 @@ typedef struct {
  * ORDERMOE_EWORKSPACE): row tables, the activations, the per-row outputs and,
  * for bf16 batches that take the tiled GEMMs, 64 MiB of fp32 partial tiles for
  * GEMM tiles split along K (summed in K order, so results are deterministic) and
- * the GEMMs' work lists: T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E,
- * and T > 128, except T <= 160 where n_shared < 2, T k <= 20 E and the routed
- * gate/up weights take less than 64 MiB.  (A workspace smaller by the 64 MiB is
+ * the GEMMs' work lists.  With G the bytes of the routed gate/up weights
+ * (n_local * 2f * d * 2): T <= 128 where f >= 12288, n_shared < 2 and T k > 20 E, or
+ * where T > 32, n_shared >= 3 and G >= 64 MiB; and T > 128, except T <= 160 where
+ * n_shared < 2, T k <= 20 E and G < 64 MiB.  (A workspace smaller by the 64 MiB is
  * accepted, and the batch takes the untiled GEMMs, where T <= 128, and where
  * T <= 512, n_shared < 2 and T k <= 20 E.)  The
  * call uses it until the stream passes the call; calls in flight at the same

@@ -1631,9 +1631,15 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 // Up to THIN_MAX_T tokens it is the safe choice whatever rows the experts get: the
 // tiled one takes half as long again when the local experts get few rows (15
 // experts of d = 2048, f = 1408, one row: 24 us thin, 36 tiled), the thin one at
-// most twice as long when a few experts get all tokens.  Except where THIN_ROWS rows
-// per expert are the mean and one expert's gate/up tiles fill half the chip
-// (f >= TILED_F): 2 experts of f = 14336, 128 tokens, three layers in turn, 2 x 2, 2 x
+// most twice as long when a few experts get all tokens.  With two exceptions.
+// TILED_SHARED shared experts in a layer of STREAM_BYTES, above TILED_SHARED_T tokens:
+// they form one group with as many times the routed K, which the thin GEMM runs whole
+// and the tiled one in K pieces (thin over tiled time, three layers in turn, 33 to 128
+// tokens over seven row profiles, d = 2048, f = 1408, with shared rows and without any:
+// 3 shared 1.09 to 1.20 and 0.90 to 0.97; 4 shared 1.18 to 1.28 and 0.90 to 0.98, 0.63
+// at a single row in all; 2 shared 1.01 to 1.09 and 0.90 to 0.98; 4 shared of d = 1024,
+// f = 640, 20 MB: 0.75 to 0.91).  And where THIN_ROWS rows per expert are the mean and
+// one expert's gate/up tiles fill half the chip (f >= TILED_F): 2 experts of f = 14336, 128 tokens, three layers in turn, 2 x 2, 2 x
 // 32 and 2 x 128 rows: thin 136, 166 and 319 us, tiled 135, 141 and 159 (and 90 against
 // 102 at a single row); f = 12288: tiled at most the time that thin takes, f = 7168: 79
 // against 68 with few rows.
@@ -1648,7 +1654,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs c) {
 // alone 216 to 222), hot experts pay only these (8 of 320 rows: 149 us, thin 325,
 // tiled alone 145).
 constexpr int64_t THIN_MAX_T = 128, THIN_SMALL_T = 160, THIN_SPARSE_T = 512;
-constexpr int THIN_ROWS = 20, TILED_F = 12288;
+constexpr int THIN_ROWS = 20, TILED_F = 12288, TILED_SHARED = 3, TILED_SHARED_T = 32;
 // Routed gate/up weights of at least this many bytes are streamed with non-temporal
 // loads by short single row tiles and by the thin GEMM.  Tiled gate/up: 805 MB (32
 // experts of d = 4096, f = 1536) 148 -> 131 us, 92 MB (8 of d = 2048, f = 1408)
@@ -1696,7 +1702,11 @@ int forward_tokens_per_block() { return FT_TB; }
 int forward_gemms(int dtype, int64_t T, int k, int E, int f, int n_shared, int64_t gu_bytes, bool room) {
     if (dtype != ORDERMOE_BF16) return 0;
     const bool few = T * k <= (int64_t)THIN_ROWS * E;
-    if (T <= THIN_MAX_T) return few || f < TILED_F || n_shared >= 2 || !room ? GEMM_THIN : GEMM_TILED;
+    if (T <= THIN_MAX_T) {
+        const bool wide = f >= TILED_F && n_shared < 2 && !few;
+        const bool shared = n_shared >= TILED_SHARED && T > TILED_SHARED_T && gu_bytes >= STREAM_BYTES;
+        return (wide || shared) && room ? GEMM_TILED : GEMM_THIN;
+    }
     if (!few || T > THIN_SPARSE_T || n_shared >= 2) return GEMM_TILED;
     if (gu_bytes < STREAM_BYTES) return T <= THIN_SMALL_T || !room ? GEMM_THIN : GEMM_TILED;
     return room ? GEMM_THIN | GEMM_TILED : GEMM_THIN;

@@ -137,8 +137,11 @@ def test_work_lists_that_cut_tiles(rows, d, f, n_shared, here, gate_up, down):
 
 
 @pytest.mark.parametrize("T,k,E,d,f,n_shared,rows,path", [
-    (32, 4, 60, 512, 256, 4, [3, 9, 1], "thin"),
-    (33, 4, 60, 512, 256, 4, [3, 9, 1], "thin"),
+    (33, 4, 60, 512, 256, 4, [3, 9, 1], "thin"),               # four shared experts, a small layer
+    (32, 4, 60, 2048, 512, 3, [1, 2] * 8, "thin"),             # three, 64 MiB of gate/up weights
+    (33, 4, 60, 2048, 512, 3, [1, 2] * 8, "tiled"),
+    (33, 4, 60, 2048, 512, 2, [1, 2] * 8, "thin"),
+    (33, 4, 60, 2048, 512, 3, [1, 2] * 7 + [1], "thin"),       # 60 MiB
     (128, 6, 64, 512, 256, 2, [97, 31], "thin"),               # several row tiles, a shared K twice the routed one
     (129, 6, 64, 512, 256, 2, [97, 31], "tiled"),
     (129, 1, 7, 512, 256, 1, [97, 31], "thin"),                # 18.4 rows per expert

@@ -275,13 +275,14 @@ PARTIAL_TILES = 64 << 20       # workspace of the tiled bf16 GEMMs
 
 
 @pytest.mark.parametrize("d,f,E,k,n_shared", [
-    (2048, 1408, 60, 4, 4), (2048, 1408, 64, 6, 2),    # shared experts side by side: a K several times the routed one
+    (2048, 1408, 60, 4, 4),                            # four shared experts, less than 64 MiB of gate/up weights
+    (2048, 1408, 64, 6, 2),                            # two shared experts
     (512, 1024, 8, 2, 0), (4096, 7168, 8, 2, 0),       # many rows per expert by the mean, few column tiles
     (4096, 1536, 128, 8, 0),
 ])
 def test_batches_of_128_tokens_need_no_partial_tiles(d, f, E, k, n_shared):
-    """They take the thin GEMM, which no distribution of the rows makes much
-    slower, and which needs no partial tiles."""
+    """They take the thin GEMM, which needs none, outside of its two exceptions
+    (wide experts with many rows, large layers with three shared experts)."""
     ids = np.array([0, 4], np.int32)
     ex = om.Experts(dtype=om.BF16, d=d, f=f, E=E, n_local=2, n_shared=n_shared)
     ex.local_experts = ids.ctypes.data_as(ctypes.c_void_p)
